@@ -37,10 +37,10 @@ BYTES_PER_UPDATE = 9  # read V (4 B) + read obstacle code (1 B) + write V (4 B),
 TURNS = (0, 2, 3, 5)   # LF, RB, RF, LB
 # the sweep kernels of the maze workload (512-pose curves: 32-step sections)
 KERNELS = {
-    "fused_turn": "row_sweep_kernel<32, true, false, true, true> (two turn maneuvers on shared circles in one launch)",
-    "turn": "row_sweep_kernel<32, false, false, true, true> (one turn maneuver)",
-    "straight_y": "row_sweep_kernel<32, false, false, true, false> (straight maneuver, y-major planes)",
-    "straight_x": "xmajor_band_kernel<32, 256, 1> (straight maneuver, x-major planes, band tiles)",
+    "fused_turn": "row_sweep_kernel<32, true, false, true> (two turn maneuvers on shared circles in one launch)",
+    "turn": "row_sweep_kernel<32, false, false, true> (one turn maneuver)",
+    "straight_y": "row_sweep_kernel<32, false, false, true> (straight maneuver, y-major planes)",
+    "straight_x": "xmajor_band_kernel<32, 256, 1, false> (straight maneuver, x-major planes, band tiles)",
 }
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_sweeps_maze_512.json")
 

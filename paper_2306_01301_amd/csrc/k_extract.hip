@@ -205,7 +205,19 @@ __global__ __launch_bounds__(kThreads) void seed_kernel(DevPlan d) {
     sd[1] = v;
     sd[2] = (uint32_t)s;
     sd[3] = (uint32_t)k;
-    if (seed) atomicMin(d.V + q, v);
+    if (seed) {
+      atomicMin(d.V + q, v);
+      // the seed's tiles of the three kinds are new to every maneuver
+      const int N = d.nx, L = d.nt;
+      const StampLayout sl = stamp_layout(N, L);
+      for (int side = 0; side < 2; side++) {
+        const int x = wrapn(qi - d.turn_off[(2 * side) * L + qT], N), y = wrapn(qj - d.turn_off[(2 * side + 1) * L + qT], N);
+        d.stamps[(side ? sl.right : sl.left) + (size_t)(x >> 6) * N + y] = 1u;
+      }
+      const int16_t* sk = d.skew + (size_t)qT * N;
+      const int line = d.family[qT] == 0 ? wrapn(qj - sk[qi], N) : wrapn(qi - sk[qj], N);
+      d.stamps[sl.str + (size_t)(line >> 6) * L + d.slot[qT]] = 1u;
+    }
   }
 }
 

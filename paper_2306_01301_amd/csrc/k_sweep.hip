@@ -82,6 +82,17 @@ __device__ __forceinline__ uint32_t row_cell(uint32_t g, uint32_t x, uint32_t sh
   return g + wrap_col(x + shift, N);
 }
 
+// bits |= any ? bit : 0 on scalar registers (any and bits are the same in all
+// lanes; written out because the compiler folds such bits through vector
+// registers, or keeps every mask live to the end).
+__device__ __forceinline__ void set_if(uint32_t& bits, uint32_t any, uint32_t bit) {
+  uint32_t t;
+  asm("s_cmp_lg_u32 %2, 0\n\ts_cselect_b32 %1, %3, 0\n\ts_or_b32 %0, %0, %1"
+      : "+s"(bits), "=&s"(t)
+      : "s"(any), "i"(bit)
+      : "scc");
+}
+
 constexpr int kBufferWord3 = 0x00020000;  // descriptor word 3 for untyped access on gfx9-family GPUs
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -113,6 +124,145 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
 
 // Tile of workgroup slot b of n: XCD-aware (order 1) or launch order (order 2).
 __device__ __forceinline__ int tile_of(int b, int n, int order) { return order == 2 ? b : xcd_tile(b, n); }
+
+// ---- change tracking (SweepTrack) ----
+// The x tiles that hold columns first .. first + w - 1 (cyclic; first in
+// [0, N), w <= 66, w <= N); `tiles`: the stamp of x tile 0, `pitch` words per
+// x tile.  Plain stores without a test for tiles stamped twice: lanes that
+// stamp the same word share a request.
+__device__ __forceinline__ void stamp_run(GlobalPtr<uint32_t> tiles, int pitch, int first, int w, int N, uint32_t stamp) {
+  int mid = first + (w >> 1), last = first + w - 1;
+  mid -= (mid >= N) ? N : 0;
+  last -= (last >= N) ? N : 0;
+  tiles[__umul24(first >> 6, pitch)] = stamp;
+  if (w > 64) tiles[__umul24(mid >> 6, pitch)] = stamp;
+  tiles[__umul24(last >> 6, pitch)] = stamp;
+  // a short last tile may lie whole inside a run that wraps
+  if ((N & 63) != 0 && last < first) tiles[__umul24((N - 1) >> 6, pitch)] = stamp;
+}
+
+__device__ __forceinline__ int below(int v, int N) { return v < 0 ? v + N : v; }  // v in [-N, N) reduced mod N
+
+// The circle tiles (offsets ox, oy of their curves in this plane) that hold
+// the run at columns col .. col + w - 1 of row `row`.
+__device__ __forceinline__ void stamp_circles(GlobalPtr<uint32_t> st, int ox, int oy, int row, int col, int w, int N,
+                                              uint32_t stamp) {
+  stamp_run(st + below(row - oy, N), N, below(col - ox, N), w, N, stamp);
+}
+
+// The straight tiles of a plane (slope kq, straight_slope) that hold the run:
+// lines x' = column - B(row) where lines advance a row per step, else x' =
+// row - B(column) with B monotone.  B is taken from the slope, which is at
+// most one off, so the run of lines is a line wider on both sides; reading
+// the table instead would wait for every store still in flight.
+__device__ __forceinline__ int slope_at(int kq, int y) { return (__mul24(y, kq) + 1024) >> 11; }
+__device__ __forceinline__ void stamp_lines(GlobalPtr<uint32_t> st, int nt, int kq, bool x_major, int row, int col,
+                                            int w, int N, uint32_t stamp) {
+  const int end = col + w - 1;
+  // the columns up to the end of the row (x-major: a wrapped rest starts another line run)
+  const int b0 = (x_major && end >= N) ? N - 1 : end;
+  const int ba = slope_at(kq, x_major ? col : row), bb = x_major ? slope_at(kq, b0) : ba;
+  int x = (x_major ? row : col) - 1 - (ba > bb ? ba : bb);
+  const int n = (x_major ? (ba > bb ? ba - bb : bb - ba) : w - 1) + 3;
+  x = below(below(x, N), N);
+  x -= (x >= N) ? N : 0;
+  stamp_run(st, nt, x, n < N ? n : N, N, stamp);
+  if (x_major && end >= N) {
+    const int bc = slope_at(kq, end - N);
+    int y = row - 1 - (bc > 0 ? bc : 0);
+    const int m = (bc > 0 ? bc : -bc) + 3;
+    y = below(y, N);
+    y -= (y >= N) ? N : 0;
+    stamp_run(st, nt, y, m < N ? m : N, N, stamp);
+  }
+}
+
+// A plane's slope in 1/2048, from the last entry of its skew table.
+__device__ __forceinline__ int straight_slope(int b_last, int N) {
+  const int d = 2 * (N - 1), v = 2 * 2048 * b_last;
+  const int k = (v + (v < 0 ? -(N - 1) : N - 1)) / d;
+  return k > 2047 ? 2047 : (k < -2047 ? -2047 : k);
+}
+
+// Stamp of tile t of a job.
+__device__ __forceinline__ GlobalPtr<uint32_t> own_stamp(const SweepJob& a, int t) {
+  const int outer = t / a.tiles_x, tx = t - outer * a.tiles_x;
+  return as_global(a.tr.stamps) + (a.tr.own + (uint32_t)tx * a.tr.pitch + (uint32_t)outer);
+}
+__device__ __forceinline__ uint32_t tile_stamp(const SweepJob& a, int t) { return *own_stamp(a, t); }
+
+// The tiles a workgroup of a tracked launch visits when the launch has more
+// tiles than workgroups.  Every workgroup reads the stamps of the job's tiles
+// (at most 16384) once: a wave ballot gives 64 tiles' bits, a prefix sum of
+// their counts the rank of every active tile, and ranks are dealt to the
+// workgroups as tiles are in an untracked launch: a contiguous eighth of them
+// to each XCD (order 1), round-robin over its workgroups.
+struct ActiveTiles {
+  static constexpr int kMaxTiles = 16384, kMinGrid = 256;
+  uint64_t bits[kMaxTiles / 64];
+  uint32_t before[kMaxTiles / 64];  // active tiles in the words before this one
+  uint32_t total;
+  uint16_t list[kMaxTiles / kMinGrid];
+};
+
+// Fills at.list with this workgroup's tiles and returns their number.
+__device__ __forceinline__ int build_active(ActiveTiles& at, const SweepJob& a) {
+  const int tiles = a.blocks, order = a.order;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int words = (tiles + 63) >> 6;
+  constexpr int R = 4;  // words per round: their loads go out together
+  for (int w0 = wave; w0 < words; w0 += R * waves) {
+    uint32_t st[R];
+#pragma unroll
+    for (int e = 0; e < R; e++) {
+      const int t = 64 * (w0 + e * waves) + lane;
+      st[e] = tile_stamp(a, t < tiles ? t : tiles - 1);
+    }
+#pragma unroll
+    for (int e = 0; e < R; e++) {
+      const int w = w0 + e * waves, t = 64 * w + lane;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(t < tiles && st[e] > a.tr.thr);
+      if (lane == 0 && w < words) at.bits[w] = m;
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    uint32_t run = 0;
+    for (int w0 = 0; w0 < words; w0 += 64) {
+      const int w = w0 + lane;
+      const uint32_t n = w < words ? (uint32_t)__builtin_popcountll(at.bits[w]) : 0u;
+      uint32_t sum = n;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(sum, o, 64);
+        if (lane >= o) sum += y;
+      }
+      if (w < words) at.before[w] = run + sum - n;
+      run += __shfl(sum, 63, 64);
+    }
+    if (lane == 0) at.total = run;
+  }
+  __syncthreads();
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane((int)at.total);
+  // this workgroup's ranks: first, first + step, ... below end
+  uint32_t first = blockIdx.x, step = gridDim.x, end = total;
+  if (order != 2) {
+    const uint32_t x = blockIdx.x & 7u, per = total >> 3, rem = total & 7u;
+    const uint32_t base = x * per + (x < rem ? x : rem);
+    first = base + (blockIdx.x >> 3);
+    step = (gridDim.x - x + 7u) >> 3;  // workgroups of this XCD
+    end = base + per + (x < rem ? 1u : 0u);
+  }
+  for (int w = wave; w < words; w += waves) {
+    const uint64_t m = at.bits[w];
+    const uint32_t r = at.before[w] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    if (((m >> lane) & 1u) && r >= first && r < end && (r - first) % step == 0)
+      at.list[(r - first) / step] = (uint16_t)(64 * w + lane);
+  }
+  __syncthreads();
+  return first < end ? (int)((end - first + step - 1u) / step) : 0;
+}
 
 // Value entering this wave's section: the cyclic fixed point (turns) or the
 // composition of the earlier sections from INF (straights).  Sections are
@@ -150,6 +300,11 @@ struct RowShared {
   uint32_t row_base[1024]; // per step: index of the first pose of the row it reads
                            // (power-of-two N: OR the column offset below)
   uint16_t shift[1024];    // per step: column offset of curve x' (reduced mod N)
+  // tracked sweeps: per 32 steps, the steps with a changed value among the
+  // tile's first and last 32 curves
+  uint32_t changed[2][32];
+  int line[2][5];          // straights, by tile parity: the plane's circle offsets (left x, y, right x, y), direction
+  SweepTrack tr;
 };
 
 // The scan phases of one section held in registers, then its stores.
@@ -162,13 +317,24 @@ struct RowShared {
 // unchanged (memory already holds them).  The test is per wave and step: a
 // ballot in the replay, one bit per step, and a uniform branch at the store
 // (no per-lane work; a step with any change stores all its lanes).
-template <int P, bool FUSED, bool GUARD, bool POW2, bool ELIDE>
+template <int P, bool FUSED, bool GUARD, bool POW2, bool TRACK>
 __device__ __forceinline__ void scan_section(const SweepJob& a, const RowBuffers& buf, RowShared& sh,
                                              uint32_t (&u)[P], uint32_t (&code)[P], int n_real, int S, int wave,
                                              int lane, bool cyclic, bool active, int xp, int first, int N) {
   uint32_t packed[FUSED ? P / 4 : 1];
-  uint32_t changed = 0;  // bit k: some lane's value at step k changed (wave-uniform)
-  static_assert(!ELIDE || P <= 32, "one bit per step");
+  // bit k: some value at step k changed (wave-uniform); tracked sweeps keep
+  // the first and the last 32 lanes apart
+  uint32_t lo = 0, hi = 0;
+  auto note = [&](int k, uint32_t before, uint32_t after) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(after != before);
+    if (TRACK) {
+      set_if(lo, (uint32_t)m, 1u << k);
+      set_if(hi, (uint32_t)(m >> 32), 1u << k);
+    } else {
+      set_if(lo, (uint32_t)m | (uint32_t)(m >> 32), 1u << k);
+    }
+  };
+  static_assert(P <= 32, "one bit per step");
   {
     // weights replace the codes; compose the section into (D, C):
     // min(C + w, u + ct + w) = min(C, u + ct) + w (saturating add is monotone).
@@ -178,8 +344,7 @@ __device__ __forceinline__ void scan_section(const SweepJob& a, const RowBuffers
     uint32_t D = 0, C = kInf;
     if (FUSED) {
 #pragma unroll
-      for (int q = 0; q < P / 4; q++)
-      {
+      for (int q = 0; q < P / 4; q++) {
         packed[q] = code[4 * q] | (code[4 * q + 1] << 8) | (code[4 * q + 2] << 16) | (code[4 * q + 3] << 24);
         asm volatile("" : "+v"(packed[q]));  // keep the packed form (not P live codes)
       }
@@ -201,19 +366,14 @@ __device__ __forceinline__ void scan_section(const SweepJob& a, const RowBuffers
     uint32_t v = section_carry(sh.aggD, sh.aggC, S, wave, lane, cyclic);
     // replay: a hard pose has weight INF, and w >> 31 (arithmetic) is then
     // all ones, which forces its output to INF (weights of other codes stay
-    // below 2^24).  A fused pair forces it only in the second replay: until
-    // then a hard pose's value only ever enters a step whose weight is INF,
-    // which returns INF whatever the value, so it cannot change any result.
+    // below 2^24).  (In the first replay of a fused pair this changes no
+    // result, but a hard pose would count as changed in every pass.)
 #pragma unroll
     for (int k = 0; k < P; k++) {
       const uint32_t w = code[k];
       const uint32_t uu = u[k];
-      u[k] = FUSED ? umin(v, uu) : (umin(v, uu) | (uint32_t)((int32_t)w >> 31));
-      if (ELIDE) {
-        // fold each step's mask into its bit now (not 32 masks held in registers)
-        changed = (uint32_t)__builtin_amdgcn_readfirstlane(
-            (int)(changed | ((__builtin_amdgcn_ballot_w64(u[k] != uu) != 0ull ? 1u : 0u) << k)));
-      }
+      u[k] = umin(v, uu) | (uint32_t)((int32_t)w >> 31);
+      note(k, uu, u[k]);
       v = sadd(umin(v, sadd(uu, a.ct)), w);
     }
     if (FUSED) {
@@ -241,21 +401,23 @@ __device__ __forceinline__ void scan_section(const SweepJob& a, const RowBuffers
         const uint32_t w = code[k];
         const uint32_t uu = u[k];
         u[k] = umin(v, uu) | (uint32_t)((int32_t)w >> 31);
-        if (ELIDE) {
-          changed = (uint32_t)__builtin_amdgcn_readfirstlane(
-              (int)(changed | ((__builtin_amdgcn_ballot_w64(u[k] != uu) != 0ull ? 1u : 0u) << k)));
-        }
+        note(k, uu, u[k]);
         v = sadd(umin(v, sadd(uu, a.ct2)), w);
       }
     }
   }
+  if (TRACK && lane == 0) {
+    sh.changed[0][wave] = lo;
+    sh.changed[1][wave] = hi;
+  }
+  const uint32_t changed = lo | hi;
   // recompute the pose of every step rather than keeping P of them live
   int xs = xp;
   asm volatile("" : "+v"(xs));
   if (active) {
 #pragma unroll
     for (int k = 0; k < P; k++) {
-      if ((!GUARD || k < n_real) && (!ELIDE || ((changed >> k) & 1u))) {
+      if ((!GUARD || k < n_real) && ((changed >> k) & 1u)) {
         buffer_store_u32(u[k], buf.V,
                          row_cell<POW2>(sh.row_base[first + k], (uint32_t)xs, POW2 ? 0u : sh.shift[first + k], N), 0,
                          0, 0);
@@ -280,10 +442,10 @@ __device__ __forceinline__ void scan_section_wide(const SweepJob& a, const RowBu
   __shared__ uint32_t upper[16][P - H][64];
   // write elision, as in scan_section: bit k of changed[k / 32] says some
   // lane's value at step k changed (wave-uniform)
-  uint32_t changed[(P + 31) / 32] = {};
+  uint32_t changed[2] = {};
   auto note = [&](int k, uint32_t before, uint32_t after) {
-    changed[k >> 5] = (uint32_t)__builtin_amdgcn_readfirstlane(
-        (int)(changed[k >> 5] | ((__builtin_amdgcn_ballot_w64(after != before) != 0ull ? 1u : 0u) << (k & 31))));
+    const uint64_t m = __builtin_amdgcn_ballot_w64(after != before);
+    set_if(changed[k >> 5], (uint32_t)m | (uint32_t)(m >> 32), 1u << (k & 31));
   };
   uint32_t (*hi)[64] = upper[wave];
   uint32_t u[H], packed[P / 4];
@@ -353,8 +515,7 @@ __device__ __forceinline__ void scan_section_wide(const SweepJob& a, const RowBu
       const bool real = !GUARD || k < n_real;
       const uint32_t w = real ? weight_of(k) : 0u;
       const uint32_t uu = real ? (k < H ? u[k] : hi[k - H][lane]) : kInf;
-      // (a fused pair forces hard poses to INF only in its second replay)
-      const uint32_t out = FUSED ? umin(v, uu) : (umin(v, uu) | (uint32_t)((int32_t)w >> 31));
+      const uint32_t out = umin(v, uu) | (uint32_t)((int32_t)w >> 31);
       note(k, uu, out);
       if (k < H)
         u[k] = out;
@@ -403,6 +564,10 @@ __device__ __forceinline__ void scan_section_wide(const SweepJob& a, const RowBu
       v = sadd(umin(v, sadd(uu, a.ct2)), w);
     }
   }
+  if (lane == 0) {
+#pragma unroll
+    for (int m = 0; m < 2; m++) sh.changed[0][2 * wave + m] = sh.changed[1][2 * wave + m] = changed[m];
+  }
   int xs = xp;
   asm volatile("" : "+v"(xs));
   if (active) {
@@ -425,22 +590,114 @@ __device__ __forceinline__ void scan_section_wide(const SweepJob& a, const RowBu
 // are issued while the previous tile's stores are still draining (a global
 // read there would first wait for every earlier store).
 struct TurnGeo {
-  uint32_t Tn;  // plane T times N
-  int shift;    // column offset of the curve through x' = 0
-  int oy;       // row offset of that curve from y'
+  // shift (column offset of the curve through x' = 0), row offset of that
+  // curve from y', and column offset of the other circles: 10 bits each; top
+  // bit: the plane's straights are x-major
+  uint32_t own;
+  // tracked sweeps: row offset of the other circles and slot of the plane (10
+  // bits each), slope of the plane (straight_slope, 12 bits)
+  uint32_t other;
 };
 template <int P>
 __device__ __forceinline__ TurnGeo turn_geo(const SweepJob& a) {
-  TurnGeo g{0u, 0, 0};
-  const int L = a.L, s = threadIdx.x;
+  TurnGeo g{0u, 0u};
+  const int L = a.L, N = a.N, s = threadIdx.x;
   if (a.cyclic && s < ((L + P - 1) / P) * P) {
     const int sc = s < L ? s : L - 1;  // steps past the curve repeat the last one
     const int T = a.dir ? sc : (L - 1 - sc);
-    g.Tn = (uint32_t)T * (uint32_t)a.N;
-    g.shift = as_global(a.offx)[T];
-    g.oy = as_global(a.offy)[T];
+    g.own = (uint32_t)as_global(a.offx)[T] | ((uint32_t)as_global(a.offy)[T] << 10);
+    if (a.tr.mode != kTrackOff) {
+      const GlobalPtr<const int32_t> o = as_global(a.tr.other_off);
+      const int k = straight_slope(as_global(a.skew)[(size_t)T * N + N - 1], N);
+      const uint32_t slot = (uint32_t)as_global(a.tr.slot)[T];
+      g.own |= ((uint32_t)o[T] << 20) | (slot < (uint32_t)a.tr.n_planes_x ? 1u << 31 : 0u);
+      g.other = (uint32_t)o[L + T] | (slot << 10) | ((uint32_t)k << 20);
+    }
   }
   return g;
+}
+
+// What thread s keeps of step s between tiles: the job's turn geometry and,
+// for the stamps of straights, the column offset it had in the tile before.
+// Tracked sweeps keep it in LDS (only its own thread touches an entry) where
+// there is room: in registers it is spilled, and reading a spilled register
+// back waits for every store in flight (fused turn pass of a 512^2 x 256 plan
+// 145 against 138 us).  The 64-step sections leave no room, and do not spill.
+constexpr bool steps_in_lds(int P, bool track) { return track && P <= 32; }
+template <int P, bool LDS>
+struct StepStore {};
+template <int P>
+struct StepStore<P, true> {
+  static constexpr int kSteps = 16 * P;
+  TurnGeo geo[kSteps];
+  uint16_t shift[kSteps];
+};
+
+template <int P, bool LDS>
+struct StepKeep {
+  TurnGeo g{0u, 0u};
+  int s = 0;
+  __device__ __forceinline__ explicit StepKeep(StepStore<P, LDS>&) {}
+  __device__ __forceinline__ void set_geo(TurnGeo v) { g = v; }
+  __device__ __forceinline__ TurnGeo geo() const { return g; }
+  __device__ __forceinline__ void set_shift(int v) { s = v; }
+  __device__ __forceinline__ int shift() const { return s; }
+};
+template <int P>
+struct StepKeep<P, true> {
+  using Store = StepStore<P, true>;
+  Store& st;
+  __device__ __forceinline__ explicit StepKeep(Store& s) : st(s) {}
+  __device__ __forceinline__ void set_geo(TurnGeo g) {
+    if (threadIdx.x < Store::kSteps) st.geo[threadIdx.x] = g;
+  }
+  __device__ __forceinline__ TurnGeo geo() const { return st.geo[threadIdx.x % Store::kSteps]; }
+  __device__ __forceinline__ void set_shift(int v) {
+    if (threadIdx.x < Store::kSteps) st.shift[threadIdx.x] = (uint16_t)v;
+  }
+  __device__ __forceinline__ int shift() const { return st.shift[threadIdx.x % Store::kSteps]; }
+};
+
+// Stamps of the tiles that hold changed poses of the tile swept before:
+// thread s looks at step s (a barrier after the sweep has written sh.changed,
+// and another before the next sweep writes it).  Reads no global memory, so
+// nothing here waits for stores in flight.
+template <int P, bool FUSED, bool POW2>
+__device__ __forceinline__ void stamp_changes(const SweepJob& a, int tile, int parity, const RowShared& sh,
+                                              const StepKeep<P, steps_in_lds(P, true)>& keep) {
+  int s = threadIdx.x;
+  asm volatile("" : "+v"(s));  // nothing of this is worked out ahead and kept over the tile loop (registers)
+  const int N = a.N, L = a.L;
+  if (s >= L) return;
+  const int word = (s / P) * (P > 32 ? 2 : 1) + ((s % P) >> 5), bit = (s % P) & 31;
+  const bool lo = (sh.changed[0][word] >> bit) & 1u, hi = (sh.changed[1][word] >> bit) & 1u;
+  if (!lo && !hi) return;
+  const bool cyclic = FUSED || a.cyclic != 0;
+  const SweepTrack& tr = sh.tr;
+  const GlobalPtr<uint32_t> st = as_global(tr.stamps);
+  const uint32_t stamp = tr.mark_stamp;
+  const int tiles_x = a.tiles_x, per = tiles_x * N;
+  const int outer = POW2 ? tile >> __builtin_ctz(tiles_x) : tile / tiles_x, tx = tile - outer * tiles_x;
+  st[tr.own + (uint32_t)tx * tr.pitch + (uint32_t)outer] = tr.own_stamp;
+  // the changed part of the tile's columns of this row
+  const int c0 = 64 * tx + (lo ? 0 : 32), c1 = 64 * tx + (hi ? 64 : 32), w = (c1 < N ? c1 : N) - c0;
+  if (w <= 0) return;
+  if (cyclic) {
+    const TurnGeo g = keep.geo();
+    int row = outer + (int)((g.own >> 10) & 1023u), col = c0 + (int)(g.own & 1023u);
+    row -= (row >= N) ? N : 0;
+    col -= (col >= N) ? N : 0;
+    stamp_circles(st + tr.circles, (int)((g.own >> 20) & 1023u), (int)(g.other & 1023u), row, col, w, N, stamp);
+    stamp_lines(st + 2 * per + ((g.other >> 10) & 1023u), L, (int32_t)g.other >> 20, (g.own >> 31) != 0u, row, col, w, N,
+                stamp);
+  } else {
+    const int* o = sh.line[parity];
+    const int row = o[4] ? s : L - 1 - s;
+    int col = c0 + keep.shift();
+    col -= (col >= N) ? N : 0;
+    stamp_circles(st, o[0], o[1], row, col, w, N, stamp);
+    stamp_circles(st + per, o[2], o[3], row, col, w, N, stamp);
+  }
 }
 
 // Row-coalesced sweep of one tile (64 curves) of a job: turns (cyclic) and
@@ -452,13 +709,16 @@ __device__ __forceinline__ TurnGeo turn_geo(const SweepJob& a) {
 // the pair costs one read and one write per pose.
 // The workgroup has exactly one wave per section (64 S threads: the
 // launchers size it so); a workgroup of another size skips the tile.
-// POW2: N is a power of two.  g: the job's turn geometry (turn_geo).
-template <int P, bool FUSED, bool GUARD, bool POW2>
-__device__ __forceinline__ void row_sweep_tile(const SweepJob& a, int tile, RowShared& sh, const TurnGeo& g) {
+// POW2: N is a power of two.  swept: the tile this workgroup swept before,
+// whose changes are stamped once this tile's loads are on their way (-1:
+// none).
+template <int P, bool FUSED, bool GUARD, bool POW2, bool TRACK>
+__device__ __forceinline__ void row_sweep_tile(const SweepJob& a, int tile, int parity, RowShared& sh,
+                                               StepKeep<P, steps_in_lds(P, TRACK)>& keep, int swept) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int N = a.N, L = a.L;
-  const bool cyclic = a.cyclic != 0;
+  const bool cyclic = FUSED || a.cyclic != 0;
   const int S = (L + P - 1) / P;  // sections of this job
   if ((int)blockDim.x != 64 * S) return;  // uniform over the workgroup
   const int tx = tile % a.tiles_x;
@@ -476,6 +736,9 @@ __device__ __forceinline__ void row_sweep_tile(const SweepJob& a, int tile, RowS
     Lq = as_global(a.edge_len)[T0];
     dir = (as_global(a.fwd)[T0] > 0) == (a.mu_forward != 0);
     sk = as_global(a.skew) + (size_t)T0 * N;
+    if (TRACK && threadIdx.x < 4)
+      sh.line[parity][threadIdx.x] = as_global(a.tr.turn_off)[(int)threadIdx.x * a.tr.nt + T0];
+    if (TRACK && threadIdx.x == 0) sh.line[parity][4] = dir;
   }
   for (int c = threadIdx.x; c < 256; c += blockDim.x) {
     sh.wlut[c] = weight((uint32_t)c, 256u * Lq + 128u, 4u * Lq);
@@ -487,13 +750,16 @@ __device__ __forceinline__ void row_sweep_tile(const SweepJob& a, int tile, RowS
   // Steps past the curve (the last section's tail when L is not a multiple
   // of P) repeat the geometry of the last step, so loads need no clamp.
   // (one step per thread: S P <= 64 S threads)
+  int shift = 0;
   if (const int s = threadIdx.x; s < S * P) {
     uint32_t Tn;
-    int row, shift;
+    int row;
     if (cyclic) {
-      Tn = g.Tn;
-      shift = g.shift;
-      row = outer + g.oy;
+      const TurnGeo g = keep.geo();
+      const int sc = s < L ? s : L - 1;
+      Tn = (uint32_t)(dir ? sc : (L - 1 - sc)) * (uint32_t)N;
+      shift = (int)(g.own & 1023u);
+      row = outer + (int)((g.own >> 10) & 1023u);
       row -= (row >= N) ? N : 0;
     } else {
       Tn = (uint32_t)T0 * (uint32_t)N;
@@ -518,27 +784,42 @@ __device__ __forceinline__ void row_sweep_tile(const SweepJob& a, int tile, RowS
   const int n_real = (L - wave * P) < P ? (L - wave * P) : P;  // real steps of this wave
   const int first = wave * P;
   if constexpr (P >= 64) {
-    scan_section_wide<P, FUSED, GUARD, POW2>(a, buf, sh, n_real, S, wave, lane, cyclic, active, xp, first, L, N);
-    return;
-  }
-  uint32_t u[P];
-  uint32_t code[P];
-  {
-    // Load this wave's section of the 64 curves.  Lanes past the grid edge
-    // read a valid cell, so the loads carry no branch; lanes are independent
-    // curves, so an idle lane's values are never stored.
-    const int xl = active ? xp : N - 1;
-#pragma unroll
-    for (int k = 0; k < P; k++) {
-      // the geometry reads take constant offsets from one address (steps past
-      // the curve have a copy of the last step's geometry)
-      const int s = first + k;
-      const uint32_t cell = row_cell<POW2>(sh.row_base[s], (uint32_t)xl, POW2 ? 0u : sh.shift[s], N);
-      u[k] = buffer_load_u32(buf.V, cell, 0, 0, 0);
-      code[k] = buffer_load_u8(buf.B, cell, 0, 0, 0);
+    if constexpr (TRACK) {
+      if (swept >= 0) stamp_changes<P, FUSED, POW2>(a, swept, parity ^ 1, sh, keep);
+      if (!cyclic) keep.set_shift(shift);
     }
+    scan_section_wide<P, FUSED, GUARD, POW2>(a, buf, sh, n_real, S, wave, lane, cyclic, active, xp, first, L, N);
+  } else {
+    // Short sections stamp the tile before first (with their loads in registers
+    // the stamps would cost them a resident wave per SIMD), 32-step ones while
+    // their loads are on the way.
+    if constexpr (TRACK && P < 32) {
+      if (swept >= 0) stamp_changes<P, FUSED, POW2>(a, swept, parity ^ 1, sh, keep);
+    }
+    uint32_t u[P];
+    uint32_t code[P];
+    {
+      // Load this wave's section of the 64 curves.  Lanes past the grid edge
+      // read a valid cell, so the loads carry no branch; lanes are independent
+      // curves, so an idle lane's values are never stored.
+      const int xl = active ? xp : N - 1;
+#pragma unroll
+      for (int k = 0; k < P; k++) {
+        // the geometry reads take constant offsets from one address (steps past
+        // the curve have a copy of the last step's geometry)
+        const int s = first + k;
+        const uint32_t cell = row_cell<POW2>(sh.row_base[s], (uint32_t)xl, POW2 ? 0u : sh.shift[s], N);
+        u[k] = buffer_load_u32(buf.V, cell, 0, 0, 0);
+        code[k] = buffer_load_u8(buf.B, cell, 0, 0, 0);
+      }
+    }
+    if constexpr (TRACK && P == 32) {
+      if (swept >= 0) stamp_changes<P, FUSED, POW2>(a, swept, parity ^ 1, sh, keep);
+    }
+    if (TRACK && !FUSED && !cyclic)
+      keep.set_shift(POW2 ? (int)(sh.row_base[threadIdx.x & 1023] & (uint32_t)(N - 1)) : (int)sh.shift[threadIdx.x & 1023]);
+    scan_section<P, FUSED, GUARD, POW2, TRACK>(a, buf, sh, u, code, n_real, S, wave, lane, cyclic, active, xp, first, N);
   }
-  scan_section<P, FUSED, GUARD, POW2, (P <= 32)>(a, buf, sh, u, code, n_real, S, wave, lane, cyclic, active, xp, first, N);
 }
 
 // x-major straights (|tan| <= 1): line x' visits (c, x' + B(c)), so lines
@@ -746,6 +1027,7 @@ struct XBand {
   alignas(16) int16_t skew[1024];  // B(c, T) of this plane (read 8 entries at a time)
   int16_t first_col[1024];         // first column c with |B(c) - B(0)| = i (B is monotone in unit steps)
   uint8_t dirty[2][BROWS];         // band rows holding a changed value, by chunk parity
+  int off[4];                      // tracked sweeps: the plane's circle offsets (left x, y, right x, y)
 };
 
 // Where this thread's group of 4 columns sits in a chunk's band: record
@@ -759,7 +1041,7 @@ struct BandGroup {
 
 // `chunks` counts the chunks this workgroup has swept (across tiles): its
 // parity selects the band-row change flags of a chunk, which start cleared.
-template <int Q_, int NT, int BUFS, bool PREF>
+template <int Q_, int NT, int BUFS, bool PREF, bool TRACK>
 __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XBand<Q_, NT, BUFS>& sh,
                                                  uint32_t& chunks) {
   using X = XBand<Q_, NT, BUFS>;
@@ -786,6 +1068,7 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
   for (int c = tid; c < 256; c += NT) sh.wlut[c] = weight((uint32_t)c, 256u * Lq + 128u, 4u * Lq);
   const int dir = (as_global(a.fwd)[T] > 0) == (a.mu_forward != 0);
   const GlobalPtr<const int16_t> skg = as_global(a.skew) + (size_t)T * N;
+  if (TRACK && tid < 4) sh.off[tid] = as_global(a.tr.turn_off)[tid * a.tr.nt + T];
   const int b0 = skg[0];
   const bool incr = skg[N - 1] >= b0;  // B ascends with the column (else descends)
   for (int c = tid; c < N; c += NT) {
@@ -994,6 +1277,16 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
     for (int s = gfirst; s < gfirst + WPG; s++) carry = umin(sadd(carry, sh.aggD[s][lane]), sh.aggC[s][lane]);
     __syncthreads();
 
+    if (TRACK && tid < BROWS && sh.dirty[par][tid]) {
+      int row = band_row0(bmin) + tid;
+      while (row >= N) row -= N;
+      const int c0 = dir ? k0 : (N - k0 - nq);  // the chunk's first column in memory order
+      const GlobalPtr<uint32_t> st = as_global(a.tr.stamps);
+      stamp_circles(st, sh.off[0], sh.off[1], row, c0, nq, N, a.tr.mark_stamp);
+      stamp_circles(st + a.tiles_x * N, sh.off[2], sh.off[3], row, c0, nq, N, a.tr.mark_stamp);
+      *own_stamp(a, tile) = a.tr.own_stamp;
+    }
+
     // store the band: a group the tile owns whole in one 16-byte store, then
     // the owned cells of the partly owned groups found above; a band row
     // whose values all stayed as loaded is not stored (memory holds them)
@@ -1069,10 +1362,44 @@ __device__ __forceinline__ int find_job(const SweepJob* __restrict__ jobs, int n
 template <int P, bool FUSED, bool GUARD, bool POW2>
 __global__ __launch_bounds__(1024) void row_sweep_kernel(SweepJob job) {
   __shared__ RowShared sh;
-  const TurnGeo g = turn_geo<P>(job);
+  StepStore<P, false> none;
+  StepKeep<P, false> keep(none);
+  keep.set_geo(turn_geo<P>(job));
   for (int b = blockIdx.x; b < job.blocks; b += gridDim.x) {
     __syncthreads();
-    row_sweep_tile<P, FUSED, GUARD, POW2>(job, tile_of(b, job.blocks, job.order), sh, g);
+    row_sweep_tile<P, FUSED, GUARD, POW2, false>(job, tile_of(b, job.blocks, job.order), 0, sh, keep, -1);
+  }
+}
+
+// The same with the tiles' stamps (SweepTrack): visits the active tiles only
+// and stamps what their changes reach.
+template <int P, bool FUSED, bool GUARD, bool POW2>
+__global__ __launch_bounds__(1024) void row_track_kernel(SweepJob job) {
+  constexpr bool LDS = steps_in_lds(P, true);
+  __shared__ RowShared sh;
+  __shared__ ActiveTiles at;
+  __shared__ StepStore<P, LDS> store;
+  StepKeep<P, LDS> keep(store);
+  const TurnGeo geo = turn_geo<P>(job);  // (on its way while the active tiles are found)
+  if (threadIdx.x == 0) sh.tr = job.tr;  // (read after the tiles' barriers)
+  const bool skip = job.tr.mode == kTrackSkip;
+  // with a workgroup per tile each looks at its own tile's stamp only
+  const bool listed = skip && job.blocks > (int)gridDim.x;
+  const int n = listed ? build_active(at, job) : job.blocks;
+  keep.set_geo(geo);
+  int swept = -1;  // tile whose changes are still to be stamped
+  int parity = 0;
+  for (int b = listed ? 0 : blockIdx.x; b < n; b += listed ? 1 : gridDim.x) {
+    const int tile = listed ? __builtin_amdgcn_readfirstlane((int)at.list[b]) : tile_of(b, n, job.order);
+    if (skip && !listed && tile_stamp(job, tile) <= job.tr.thr) continue;
+    __syncthreads();
+    row_sweep_tile<P, FUSED, GUARD, POW2, true>(job, tile, parity, sh, keep, swept);
+    swept = tile;
+    parity ^= 1;
+  }
+  if (swept >= 0) {
+    __syncthreads();
+    stamp_changes<P, FUSED, POW2>(job, swept, parity ^ 1, sh, keep);
   }
 }
 
@@ -1080,18 +1407,19 @@ template <int P, bool FUSED, bool GUARD, bool POW2>
 __global__ __launch_bounds__(1024) void row_sweep_batch_kernel(const SweepJob* __restrict__ jobs, int n_jobs,
                                                                  int total_blocks, int order) {
   __shared__ RowShared sh;
-  int jg = -1;  // job whose turn geometry g holds
-  TurnGeo g{0u, 0, 0};
+  int jg = -1;  // job whose turn geometry is kept
+  StepStore<P, false> none;
+  StepKeep<P, false> keep(none);
   for (int b = blockIdx.x; b < total_blocks; b += gridDim.x) {
     __syncthreads();
     const int t = tile_of(b, total_blocks, order);
     const int j = __builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, t));
     const SweepJob job = jobs[j];
     if (j != jg) {
-      g = turn_geo<P>(job);
+      keep.set_geo(turn_geo<P>(job));
       jg = j;
     }
-    row_sweep_tile<P, FUSED, GUARD, POW2>(job, t - job.first_block, sh, g);
+    row_sweep_tile<P, FUSED, GUARD, POW2, false>(job, t - job.first_block, 0, sh, keep, -1);
   }
 }
 
@@ -1145,13 +1473,16 @@ constexpr int xband_waves_per_simd() { return xband_wg_per_cu<Q, NT, BUFS>() * (
 // resident workgroups (2-5 % faster at 1024 sides, 0-3 % at 512).
 constexpr int kXBandGridPerCU = 16;
 
-template <int Q, int NT, int BUFS>
+template <int Q, int NT, int BUFS, bool TRACK>
 __global__ __launch_bounds__(NT, (xband_waves_per_simd<Q, NT, BUFS>())) void xmajor_band_kernel(SweepJob job) {
   __shared__ XBand<Q, NT, BUFS> sh;
   for (int i = threadIdx.x; i < 2 * XBand<Q, NT, BUFS>::BROWS; i += NT) sh.dirty[i & 1][i >> 1] = 0;
   uint32_t chunks = 0;  // (the tile's first barrier orders the clearing before any flag is set)
-  for (int b = blockIdx.x; b < job.blocks; b += gridDim.x)
-    xmajor_band_tile<Q, NT, BUFS, XBPREF>(job, tile_of(b, job.blocks, job.order), sh, chunks);
+  for (int b = blockIdx.x; b < job.blocks; b += gridDim.x) {
+    const int tile = tile_of(b, job.blocks, job.order);
+    if (TRACK && job.tr.mode == kTrackSkip && tile_stamp(job, tile) <= job.tr.thr) continue;
+    xmajor_band_tile<Q, NT, BUFS, XBPREF, TRACK>(job, tile, sh, chunks);
+  }
 }
 
 template <int Q, int NT, int BUFS>
@@ -1163,7 +1494,7 @@ __global__ __launch_bounds__(NT, (xband_waves_per_simd<Q, NT, BUFS>())) void xma
   const SweepJob job = jobs[j];
   for (int i = threadIdx.x; i < 2 * XBand<Q, NT, BUFS>::BROWS; i += NT) sh.dirty[i & 1][i >> 1] = 0;
   uint32_t chunks = 0;
-  xmajor_band_tile<Q, NT, BUFS, XBPREF>(job, t - job.first_block, sh, chunks);
+  xmajor_band_tile<Q, NT, BUFS, XBPREF, false>(job, t - job.first_block, sh, chunks);
 }
 
 // (six transposed tiles of 27 KB fit a CU)
@@ -1190,41 +1521,29 @@ int xmajor_grid(int blocks, int per_cu) {
   return blocks < cap ? blocks : cap;
 }
 
-__global__ void init_kernel(uint32_t* __restrict__ V, size_t n4, uint32_t start) {
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < n4; q += stride) {
+__device__ __forceinline__ void init_volume(const InitJob& j) {
+  const size_t stride = (size_t)gridDim.x * blockDim.x, id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (size_t q = id; q < j.n_stamps; q += stride)
+    j.stamps[q] = (q == j.marked[0] || q == j.marked[1] || q == j.marked[2]) ? 1u : 0u;
+  for (size_t q = id; q < j.n4; q += stride) {
     const size_t e = q * 4;
     uint4 v = make_uint4(kInf, kInf, kInf, kInf);
-    if (start >= e && start < e + 4) {
-      const uint32_t o = (uint32_t)(start - e);
+    if (j.start >= e && j.start < e + 4) {
+      const uint32_t o = (uint32_t)(j.start - e);
       if (o == 0) v.x = 0;
       if (o == 1) v.y = 0;
       if (o == 2) v.z = 0;
       if (o == 3) v.w = 0;
     }
-    reinterpret_cast<uint4*>(V)[q] = v;
+    reinterpret_cast<uint4*>(j.V)[q] = v;
   }
 }
 
-// Batched init: job k fills V of plan k (n4[k] uint4 words, start index
-// start[k]); blocks stride over all plans' words.
+__global__ void init_kernel(InitJob job) { init_volume(job); }
+
+// Batched init: job k fills V of plan k; blocks stride over all plans' words.
 __global__ void init_batch_kernel(const InitJob* __restrict__ jobs, int n_jobs) {
-  for (int k = 0; k < n_jobs; k++) {
-    const InitJob j = jobs[k];
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < j.n4; q += stride) {
-      const size_t e = q * 4;
-      uint4 v = make_uint4(kInf, kInf, kInf, kInf);
-      if (j.start >= e && j.start < e + 4) {
-        const uint32_t o = (uint32_t)(j.start - e);
-        if (o == 0) v.x = 0;
-        if (o == 1) v.y = 0;
-        if (o == 2) v.z = 0;
-        if (o == 3) v.w = 0;
-      }
-      reinterpret_cast<uint4*>(j.V)[q] = v;
-    }
-  }
+  for (int k = 0; k < n_jobs; k++) init_volume(jobs[k]);
 }
 
 __global__ void walls_kernel(uint8_t* __restrict__ B, int N, int L) {
@@ -1312,7 +1631,7 @@ bool can_fuse(const DevPlan& d) { return pick_section(d.nt) > 0; }
 // straight planes) and, for straights, an x-major job.  Returns the number of
 // jobs written (0..2), blocks counts each job's workgroups; -1 for a pair
 // that cannot share a pass (the caller splits it).
-int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj) {
+int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj, TrackState* ts) {
   if (pass.mu2 >= 0 && !(fusable(pass.mu, pass.mu2) && can_fuse(d))) return -1;
   const int mu = pass.mu;
   const int N = d.nx, L = d.nt;
@@ -1325,11 +1644,32 @@ int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj) 
   j.ct = d.ct[mu];
   j.tiles_x = tiles_x;
   j.order = knob(NHP_KNOB_TILE_ORDER, 1);
+  j.skew = d.skew;
+  const StampLayout sl = stamp_layout(N, L);
+  if (ts) {
+    const uint32_t p = ++ts->pass;
+    // visit what changed since either maneuver's last pass
+    uint32_t last = ts->last[mu];
+    if (pass.mu2 >= 0 && last != kTrackStale) {
+      const uint32_t other = ts->last[pass.mu2];
+      if (other < last || other == kTrackStale) last = other;
+    }
+    j.tr.mode = last == kTrackStale ? kTrackAll : kTrackSkip;
+    j.tr.thr = 2 * last;
+    j.tr.mark_stamp = 2 * p;
+    j.tr.own_stamp = pass.mu2 >= 0 ? 2 * p + 1 : 2 * p;
+    j.tr.stamps = d.stamps;
+    j.tr.turn_off = d.turn_off;
+    j.tr.slot = d.slot;
+    j.tr.nt = L;
+    j.tr.n_planes_x = d.n_planes_x;
+    ts->last[mu] = p;
+    if (pass.mu2 >= 0) ts->last[pass.mu2] = p;
+  }
   int n = 0;
   if (mu == NHP_SF || mu == NHP_SB) {
     j.L = N;
     j.cyclic = 0;
-    j.skew = d.skew;
     j.edge_len = d.edge_len + (size_t)mu * L;
     j.fwd = d.fwd;
     j.mu_forward = (mu == NHP_SF);
@@ -1341,6 +1681,9 @@ int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj) 
     x.tiles_x = (N + xmajor_lines(N) - 1) / xmajor_lines(N);
     x.blocks = x.tiles_x * d.n_planes_x;
     x.P = 0;
+    x.tr.own = (uint32_t)sl.str;
+    y.tr.own = (uint32_t)sl.str + (uint32_t)d.n_planes_x;
+    x.tr.pitch = y.tr.pitch = (uint32_t)L;
     row->blocks = 0;
     xmaj->blocks = 0;
     if (y.blocks) *row = y;
@@ -1361,6 +1704,10 @@ int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj) 
       j.lq2 = d.turn_lq[pass.mu2];
     }
     j.blocks = tiles_x * N;
+    j.tr.own = (uint32_t)(left ? sl.left : sl.right);
+    j.tr.pitch = (uint32_t)N;
+    j.tr.circles = (uint32_t)(left ? sl.right : sl.left);
+    j.tr.other_off = d.turn_off + (left ? 2 : 0) * L;
     *row = j;
     xmaj->blocks = 0;
     n = 1;
@@ -1368,15 +1715,23 @@ int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj) 
   return n;
 }
 
+template <int P, bool FUSED, bool GUARD, bool POW2>
+void launch_row_kernel(const SweepJob& j, hipStream_t s) {
+  const int waves = (j.L + P - 1) / P;
+  const dim3 grid(row_grid(j.blocks, waves, P)), block(64 * waves);
+  if (j.tr.mode != kTrackOff)
+    hipLaunchKernelGGL((row_track_kernel<P, FUSED, GUARD, POW2>), grid, block, 0, s, j);
+  else
+    hipLaunchKernelGGL((row_sweep_kernel<P, FUSED, GUARD, POW2>), grid, block, 0, s, j);
+}
+
 template <bool FUSED, bool GUARD, bool POW2>
 hipError_t launch_row_job_t(const SweepJob& j, hipStream_t s) {
-  const int waves = (j.L + j.P - 1) / j.P;
-  const dim3 grid(row_grid(j.blocks, waves, j.P)), block(64 * waves);
   switch (j.P) {
-    case 64: hipLaunchKernelGGL((row_sweep_kernel<64, FUSED, GUARD, POW2>), grid, block, 0, s, j); break;
-    case 32: hipLaunchKernelGGL((row_sweep_kernel<32, FUSED, GUARD, POW2>), grid, block, 0, s, j); break;
-    case 16: hipLaunchKernelGGL((row_sweep_kernel<16, FUSED, GUARD, POW2>), grid, block, 0, s, j); break;
-    case 8: hipLaunchKernelGGL((row_sweep_kernel<8, FUSED, GUARD, POW2>), grid, block, 0, s, j); break;
+    case 64: launch_row_kernel<64, FUSED, GUARD, POW2>(j, s); break;
+    case 32: launch_row_kernel<32, FUSED, GUARD, POW2>(j, s); break;
+    case 16: launch_row_kernel<16, FUSED, GUARD, POW2>(j, s); break;
+    case 8: launch_row_kernel<8, FUSED, GUARD, POW2>(j, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1395,12 +1750,26 @@ hipError_t launch_row_job(const SweepJob& j, hipStream_t s) {
   return guard ? launch_row_job_g<false, true>(j, s) : launch_row_job_g<false, false>(j, s);
 }
 
-hipError_t launch_init(const DevPlan& d, uint32_t start_index, hipStream_t s) {
-  const size_t NR = (size_t)d.nx * d.nx * d.nt;  // a multiple of 64: nx and nt are multiples of 8
-  const size_t n4 = NR / 4;
-  size_t blocks = (n4 + 255) / 256;
+hipError_t launch_init(const DevPlan& d, uint32_t start_index, const StartTiles& marked, hipStream_t s) {
+  InitJob j{};
+  j.V = d.V;
+  j.n4 = (size_t)d.nx * d.nx * d.nt / 4;  // a multiple of 16: nx and nt are multiples of 8
+  j.start = start_index;
+  j.stamps = d.stamps;
+  j.n_stamps = (uint32_t)stamp_layout(d.nx, d.nt).words;
+  for (int k = 0; k < 3; k++) j.marked[k] = marked.t[k];
+  size_t blocks = (j.n4 + 255) / 256;
   if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(init_kernel, dim3((unsigned)blocks), dim3(256), 0, s, d.V, n4, start_index);
+  hipLaunchKernelGGL(init_kernel, dim3((unsigned)blocks), dim3(256), 0, s, j);
+  return hipGetLastError();
+}
+
+hipError_t launch_clear_stamps(const DevPlan& d, hipStream_t s) {
+  InitJob j{};
+  j.stamps = d.stamps;
+  j.n_stamps = (uint32_t)stamp_layout(d.nx, d.nt).words;
+  for (uint32_t& m : j.marked) m = kNoTile;
+  hipLaunchKernelGGL(init_kernel, dim3((j.n_stamps + 255) / 256), dim3(256), 0, s, j);
   return hipGetLastError();
 }
 
@@ -1416,14 +1785,27 @@ hipError_t launch_force_walls(const DevPlan& d, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_sweep(const DevPlan& d, Pass pass, hipStream_t s) { return launch_sweep_part(d, pass, 3, s); }
+// Tracking costs a row launch about 8 us (finding the active tiles, stamping
+// the last one) and a pass with every tile active about 8 % more, and saves
+// the tiles that no change has reached.  Volumes of at least 2^26 poses gain:
+// whole plans (start, now) 512^3 maze with 20 cycles 18.1 -> 13.9 ms, 1024^2
+// x 512 with 8 cycles 31.6 -> 28.3 ms, 512^2 x 256 with 6 cycles 2.88 -> 2.85
+// ms; below, launches of 10 to 35 us lose it again (384^2 x 128, 12 cycles:
+// 1.36 -> 1.52 ms; 200^2 x 72: 0.75 -> 0.89 ms).
+bool track_sweeps(const DevPlan& d) {
+  return xmajor_wide(d.nx) && d.nx >= 64 && (size_t)d.nx * d.nx * d.nt >= (size_t)1 << 26;
+}
 
-hipError_t launch_sweep_part(const DevPlan& d, Pass pass, int parts, hipStream_t s) {
+hipError_t launch_sweep(const DevPlan& d, Pass pass, hipStream_t s, TrackState* ts) {
+  return launch_sweep_part(d, pass, 3, s, ts);
+}
+
+hipError_t launch_sweep_part(const DevPlan& d, Pass pass, int parts, hipStream_t s, TrackState* ts) {
   SweepJob row{}, xmaj{};
-  if (make_sweep_jobs(d, pass, &row, &xmaj) < 0) {
+  if (make_sweep_jobs(d, pass, &row, &xmaj, ts) < 0) {
     // a pair that cannot share a pass: one pass each
-    const hipError_t e = launch_sweep(d, Pass{pass.mu, (int8_t)-1}, s);
-    return e != hipSuccess ? e : launch_sweep(d, Pass{pass.mu2, (int8_t)-1}, s);
+    const hipError_t e = launch_sweep(d, Pass{pass.mu, (int8_t)-1}, s, ts);
+    return e != hipSuccess ? e : launch_sweep(d, Pass{pass.mu2, (int8_t)-1}, s, ts);
   }
   if (row.blocks && (parts & 1)) {
     if (!row.P) return hipErrorInvalidValue;
@@ -1434,13 +1816,15 @@ hipError_t launch_sweep_part(const DevPlan& d, Pass pass, int parts, hipStream_t
     const bool wide = xmajor_wide(xmaj.N);
     const bool one = knob(NHP_KNOB_XMAJOR_BUFFERS, wide ? XB_BUFS_BUILTIN : XBUFS_BUILTIN) == 1;
     if (wide) {
-      const dim3 block(XBNT);
-      if (one)
-        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 1>),
-                           dim3(xmajor_grid(xmaj.blocks, kXBandGridPerCU)), block, 0, s, xmaj);
+      const dim3 grid(xmajor_grid(xmaj.blocks, kXBandGridPerCU)), block(XBNT);
+      if (xmaj.tr.mode != kTrackOff && one)
+        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 1, true>), grid, block, 0, s, xmaj);
+      else if (xmaj.tr.mode != kTrackOff)
+        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 2, true>), grid, block, 0, s, xmaj);
+      else if (one)
+        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 1, false>), grid, block, 0, s, xmaj);
       else
-        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 2>),
-                           dim3(xmajor_grid(xmaj.blocks, kXBandGridPerCU)), block, 0, s, xmaj);
+        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 2, false>), grid, block, 0, s, xmaj);
     } else {
       const dim3 grid(xmajor_grid(xmaj.blocks, 6)), block(XNT);
       if (one)

@@ -57,7 +57,7 @@ int hip_fail(hipError_t e, const char* what) {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
-  size_t V, B, turn_off, skew, edge_len, fwd, family, planes, taps, extract, starts, seeds, goals, total;
+  size_t V, B, turn_off, skew, edge_len, fwd, family, planes, slot, stamps, taps, extract, starts, seeds, goals, total;
 };
 
 static_assert(NHP_MAX_GOALS * 16 >= NHP_MAX_SOFT_TABLE, "the soft-cost table lives in the goal-set buffer");
@@ -100,6 +100,10 @@ Layout layout_of(const nhp_params& p) {
   o = align256(o + (size_t)p.ntheta * 4);
   l.planes = o;
   o = align256(o + (size_t)p.ntheta * 4);
+  l.slot = o;
+  o = align256(o + (size_t)p.ntheta * 4);
+  l.stamps = o;
+  o = align256(o + nhp::stamp_layout((int)p.nx, (int)p.ntheta).words * 4);
   l.taps = o;
   o = align256(o + (size_t)p.ntheta * 2 * nhp::kMaxTaps * 4);
   l.extract = o;
@@ -143,6 +147,24 @@ std::vector<int32_t> balanced_xmajor_order(const std::vector<int32_t>& planes_x,
 }
 
 }  // namespace
+
+// The tiles of the three kinds that hold pose (i, j, T), as indices into the
+// plan's stamps.
+nhp::StartTiles nhp::start_tiles(const nhp_plan* plan, int i, int j, int T) {
+  const int N = (int)plan->p.nx, L = (int)plan->p.ntheta;
+  const HostTables& t = plan->t;
+  const StampLayout sl = stamp_layout(N, L);
+  auto mod = [N](int v) { return (v % N + N) % N; };
+  StartTiles out;
+  for (int side = 0; side < 2; side++) {
+    const int x = mod(i - t.turn_off[(size_t)(2 * side) * L + T]), y = mod(j - t.turn_off[(size_t)(2 * side + 1) * L + T]);
+    out.t[side] = (uint32_t)((side ? sl.right : sl.left) + (size_t)(x / 64) * N + y);
+  }
+  const int16_t* sk = t.skew16->data() + (size_t)T * N;
+  const int line = t.family[T] == 0 ? mod(j - sk[i]) : mod(i - sk[j]);
+  out.t[2] = (uint32_t)(sl.str + (size_t)(line / 64) * L + plan->slot[T]);
+  return out;
+}
 
 static int finish_extract(nhp_plan* plan, nhp_step* h_steps, uint32_t cap, uint32_t* n_steps, uint32_t* best_ijt,
                           uint32_t* best_index, uint32_t* goal_value_q10, uint32_t* score_q10);
@@ -219,6 +241,8 @@ int plan_create(const nhp_params* params, void* d_workspace, size_t workspace_by
   d.fwd = reinterpret_cast<int32_t*>(base + l.fwd);
   d.family = reinterpret_cast<int32_t*>(base + l.family);
   d.planes = reinterpret_cast<int32_t*>(base + l.planes);
+  d.slot = reinterpret_cast<int32_t*>(base + l.slot);
+  d.stamps = reinterpret_cast<uint32_t*>(base + l.stamps);
   d.taps = reinterpret_cast<int32_t*>(base + l.taps);
   d.extract = reinterpret_cast<uint32_t*>(base + l.extract);
   d.starts = reinterpret_cast<nhp_start*>(base + l.starts);
@@ -237,6 +261,8 @@ int plan_create(const nhp_params* params, void* d_workspace, size_t workspace_by
   const HostTables& t = plan->t;
   std::vector<int32_t> planes = balanced_xmajor_order(t.planes_x, *t.skew16, (int)params->nx);
   planes.insert(planes.end(), t.planes_y.begin(), t.planes_y.end());
+  plan->slot.resize(planes.size());
+  for (size_t k = 0; k < planes.size(); k++) plan->slot[planes[k]] = (int32_t)k;
   struct Up {
     void* dst;
     const void* src;
@@ -245,6 +271,7 @@ int plan_create(const nhp_params* params, void* d_workspace, size_t workspace_by
       {d.turn_off, t.turn_off.data(), t.turn_off.size() * 4}, {d.skew, t.skew16->data(), t.skew16->size() * 2},
       {d.edge_len, t.edge_len.data(), t.edge_len.size() * 4}, {d.fwd, t.fwd.data(), t.fwd.size() * 4},
       {d.family, t.family.data(), t.family.size() * 4},       {d.planes, planes.data(), planes.size() * 4},
+      {d.slot, plan->slot.data(), plan->slot.size() * 4},
   };
   for (const Up& u : ups) {
     e = hipMemcpyAsync(u.dst, u.src, u.n, hipMemcpyHostToDevice, plan->stream);
@@ -407,9 +434,12 @@ static hipGraphExec_t capture_passes(nhp_plan* plan, const std::vector<nhp::Pass
 // a captured graph once a plan runs more than one cycle for the second time:
 // capturing and instantiating costs more than the launches it saves on a
 // plan that is swept only once.
-static int run_cycles(nhp_plan* plan, uint32_t n_cycles) {
+// A plan whose sweeps are tracked launches its kernels directly: their
+// arguments carry the pass numbers.  ts: the run's tracking state (the volume
+// is the one the stamps describe), nullptr: untracked.
+static int run_cycles(nhp_plan* plan, uint32_t n_cycles, nhp::TrackState* ts) {
   const bool pairs = nhp::can_fuse(plan->d);
-  const bool graphs = n_cycles > 1 && plan->multi_cycle_runs++ > 0;
+  const bool graphs = !ts && n_cycles > 1 && plan->multi_cycle_runs++ > 0;
   bool skip = false;
   std::vector<nhp::Pass> passes;
   for (uint32_t n = 0; n < n_cycles; n++) {
@@ -421,7 +451,7 @@ static int run_cycles(nhp_plan* plan, uint32_t n_cycles) {
     if (graphs && g) {
       HIP_CHECK(hipGraphLaunch(g, plan->stream), "cycle graph launch");
     } else {
-      for (const nhp::Pass& q : passes) HIP_CHECK(nhp::launch_sweep(plan->d, q, plan->stream), "sweep launch");
+      for (const nhp::Pass& q : passes) HIP_CHECK(nhp::launch_sweep(plan->d, q, plan->stream, ts), "sweep launch");
     }
     skip = consumed;
   }
@@ -438,13 +468,15 @@ int sweep_n_turns(nhp_plan* plan, uint32_t si, uint32_t sj, uint32_t st, uint32_
   HIP_CHECK(hipMemcpyAsync(&code, plan->d.B + s, 1, hipMemcpyDeviceToHost, plan->stream), "start check");
   HIP_CHECK(hipStreamSynchronize(plan->stream), "start check");
   if (code == NHP_HARD) return fail(NHP_ESTART, "start pose (%u, %u, %u) is in collision", si, sj, st);
-  HIP_CHECK(nhp::launch_init(plan->d, (uint32_t)s, plan->stream), "init launch");
+  HIP_CHECK(nhp::launch_init(plan->d, (uint32_t)s, nhp::start_tiles(plan, (int)si, (int)sj, (int)st), plan->stream),
+            "init launch");
   plan->n_starts = 0;
   plan->start[0] = si;
   plan->start[1] = sj;
   plan->start[2] = st;
   plan->has_value = true;
-  return (rc = run_cycles(plan, n_cycles)) ? rc : ok();
+  nhp::TrackState ts;
+  return (rc = run_cycles(plan, n_cycles, nhp::track_sweeps(plan->d) ? &ts : nullptr)) ? rc : ok();
 }
 
 int sweep_from_set(nhp_plan* plan, const nhp_start* h_starts, uint32_t n_starts, uint32_t n_cycles) {
@@ -469,21 +501,30 @@ int sweep_from_set(nhp_plan* plan, const nhp_start* h_starts, uint32_t n_starts,
   for (uint32_t k = 0; k < n_starts; k++)
     if (codes[k] == NHP_HARD) return fail(NHP_ESTART, "start %u is in collision", k);
   // init with the start pose outside the volume: V = INF everywhere
-  HIP_CHECK(nhp::launch_init(plan->d, 0xFFFFFFFFu, plan->stream), "init launch");
+  // (the seed kernel stamps the tiles of the poses it lowers)
+  HIP_CHECK(nhp::launch_init(plan->d, 0xFFFFFFFFu, {{nhp::kNoTile, nhp::kNoTile, nhp::kNoTile}}, plan->stream),
+            "init launch");
   HIP_CHECK(nhp::launch_seed(plan->d, (int)n_starts, plan->stream), "seed launch");
   plan->n_starts = (int)n_starts;
   plan->start[0] = h_starts[0].i;
   plan->start[1] = h_starts[0].j;
   plan->start[2] = h_starts[0].T;
   plan->has_value = true;
-  return (rc = run_cycles(plan, n_cycles)) ? rc : ok();
+  nhp::TrackState ts;
+  return (rc = run_cycles(plan, n_cycles, nhp::track_sweeps(plan->d) ? &ts : nullptr)) ? rc : ok();
 }
 
 int sweep_resume(nhp_plan* plan, uint32_t n_more_cycles) {
   int rc = check_plan(plan);
   if (rc) return rc;
   if (!plan->has_value) return fail(NHP_ESTATE, "sweep_resume before sweep_n_turns");
-  return (rc = run_cycles(plan, n_more_cycles)) ? rc : ok();
+  // the caller may have written the value volume since the last sweep: the
+  // first pass of every maneuver visits all tiles
+  nhp::TrackState ts;
+  for (uint32_t& q : ts.last) q = nhp::kTrackStale;
+  const bool track = n_more_cycles > 1 && nhp::track_sweeps(plan->d);
+  if (track) HIP_CHECK(nhp::launch_clear_stamps(plan->d, plan->stream), "stamp launch");
+  return (rc = run_cycles(plan, n_more_cycles, track ? &ts : nullptr)) ? rc : ok();
 }
 
 int sweep_pass(nhp_plan* plan, int32_t first, int32_t second) {

@@ -232,6 +232,10 @@ int batch_init(nhp_batch* b, nhp_plan* const* plans, const uint32_t* starts_ijt,
     jobs[k].V = p->d.V;
     jobs[k].n4 = (size_t)p->p.nx * p->p.nx * p->p.ntheta / 4;
     jobs[k].start = (uint32_t)idx;
+    jobs[k].stamps = p->d.stamps;
+    jobs[k].n_stamps = (uint32_t)nhp::stamp_layout(p->d.nx, p->d.nt).words;
+    const nhp::StartTiles marked = nhp::start_tiles(p, (int)si, (int)sj, (int)st);
+    for (int m = 0; m < 3; m++) jobs[k].marked[m] = marked.t[m];
     max_n4 = std::max(max_n4, jobs[k].n4);
   }
   HIP_TRY(hipStreamSynchronize(b->stream), "start check");

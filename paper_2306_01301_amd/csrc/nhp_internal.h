@@ -50,6 +50,8 @@ struct DevPlan {
   int32_t* fwd;          // [nt]
   int32_t* family;       // [nt]
   int32_t* planes;       // planes_x then planes_y
+  int32_t* slot;         // [nt] place of each plane in `planes`
+  uint32_t* stamps;      // change stamps of the sweep tiles (stamp_words; see SweepTrack)
   int n_planes_x, n_planes_y;
   int32_t* taps;         // [nt][n_side + n_len] packed (dx & 0xffff) | (dy << 16): side then length
   uint32_t* extract;     // result header + steps
@@ -61,6 +63,55 @@ struct DevPlan {
   uint32_t turn_lq[6];   // host copy of the (plane-independent) turn edge lengths
   uint8_t schedule[6];
   int n_schedule;
+};
+
+// Change tracking of a run of sweeps that starts from a known volume.  The
+// poses of a plan are cut into tiles of 64 curves three ways: left circles,
+// right circles and straight lines (StampLayout), and every tile has a stamp
+// that says when one of its poses last changed.  A sweep is idempotent (a
+// curve whose poses are as a maneuver left them is not changed by running it
+// again), so a pass only has to visit the tiles stamped since its maneuver
+// last ran.  Pass number p (1, 2, ...) stamps the tiles of the other two
+// kinds that share a changed pose with 2 p, its own tile with 2 p when only
+// the other maneuver of the kind has to see the change, and with 2 p + 1 when
+// the next pass of the same maneuvers has to (a fused pair: the second
+// maneuver's changes are new to the first).  A tile is visited when its stamp
+// is above `thr`: 2 q for a maneuver last run in pass q, 0 for one that has
+// not run.  Stamps only grow and a tile's own stamp is written only by the
+// workgroup that sweeps it, so a workgroup that reads the stamps late in a
+// launch finds the same tiles active as one that reads them early.
+enum TrackMode { kTrackOff = 0, kTrackSkip = 1, kTrackAll = 2 };  // All: visit every tile, stamp changes
+struct SweepTrack {
+  int mode;
+  uint32_t thr;
+  uint32_t own_stamp, mark_stamp;
+  uint32_t* stamps;         // the plan's three arrays (StampLayout)
+  uint32_t own;             // this job's array: tile (outer, tx) of it is at own + tx pitch + outer
+  uint32_t circles;         // turns: the other circles' array
+  uint32_t pitch;
+  const int32_t* turn_off;  // the plan's [4][nt]
+  const int32_t* other_off; // turns: the other circles' two rows of turn_off
+  const int32_t* slot;      // [nt]
+  int nt, n_planes_x;
+};
+
+// The three stamp arrays: [x tile][y'] of the left and of the right circles,
+// [x tile][slot] of the straights (slot: the plane's place in DevPlan::planes,
+// so a job finds its tiles' stamps without looking their planes up).
+struct StampLayout {
+  size_t left, right, str, words;
+};
+__host__ __device__ inline StampLayout stamp_layout(int nx, int nt) {
+  const size_t tiles_x = (size_t)(nx + 63) / 64;
+  return StampLayout{0, tiles_x * nx, 2 * tiles_x * nx, 2 * tiles_x * nx + tiles_x * nt};
+}
+
+// Pass numbers of a tracked run of sweeps: the pass each maneuver last ran
+// in (0: not yet; kTrackStale: its next pass visits every tile).
+constexpr uint32_t kTrackStale = 0xFFFFFFFFu;
+struct TrackState {
+  uint32_t pass = 0;
+  uint32_t last[6] = {0, 0, 0, 0, 0, 0};
 };
 
 // One maneuver of one plan, as the sweep kernels see it.  Row jobs cover
@@ -88,6 +139,7 @@ struct SweepJob {
   // registers (fused = 1); its transition cost and edge length.
   int fused;
   uint32_t ct2, lq2;
+  SweepTrack tr;            // mode 0: every tile, no stamps
 };
 
 // A pass over the value volume: one maneuver, or two consecutive turn
@@ -118,6 +170,9 @@ struct InitJob {
   uint32_t* V;
   size_t n4;       // poses / 4
   uint32_t start;  // start pose index
+  uint32_t n_stamps;    // stamps to clear
+  uint32_t* stamps;
+  uint32_t marked[3];   // the start's tiles
   uint32_t pad;
 };
 
@@ -128,7 +183,11 @@ int set_section_steps(int len, int P);
 constexpr int kKnobs = 4;
 int set_knob(int knob, int value);
 int get_knob(int knob);
-int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj);
+// ts: the tracked run the pass belongs to (its pass number and the
+// maneuvers' last passes are moved on), or nullptr.
+int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj, TrackState* ts = nullptr);
+// Whether a plan's sweeps are worth tracking (see k_sweep.hip).
+bool track_sweeps(const DevPlan& d);
 // Whether x-major jobs of grid side N take the 4-column-load kernel (batched
 // x-major launches group their jobs by it and pass it as `pow2`).
 bool xmajor_wide(int N);
@@ -154,12 +213,20 @@ constexpr uint32_t kNoSeed = 0xFFFFFFFFu;
 // Writes the seeds of n starts (init must have set V to INF before).
 hipError_t launch_seed(const DevPlan& d, int n_starts, hipStream_t s);
 
-hipError_t launch_init(const DevPlan& d, uint32_t start_index, hipStream_t s);
+// V = NHP_INF but for the start pose (start_index 0xFFFFFFFF: none), and
+// every stamp 0 but for those of the start's three tiles (index kNoTile: none).
+constexpr uint32_t kNoTile = 0xFFFFFFFFu;
+struct StartTiles {
+  uint32_t t[3];
+};
+hipError_t launch_init(const DevPlan& d, uint32_t start_index, const StartTiles& marked, hipStream_t s);
+// Every stamp 0.
+hipError_t launch_clear_stamps(const DevPlan& d, hipStream_t s);
 hipError_t launch_force_walls(const DevPlan& d, hipStream_t s);
-hipError_t launch_sweep(const DevPlan& d, Pass pass, hipStream_t s);
+hipError_t launch_sweep(const DevPlan& d, Pass pass, hipStream_t s, TrackState* ts = nullptr);
 // Part of a pass: parts bit 0 = the row kernel (turn curves, or the y-major
 // straight planes), bit 1 = the x-major straight planes.
-hipError_t launch_sweep_part(const DevPlan& d, Pass pass, int parts, hipStream_t s);
+hipError_t launch_sweep_part(const DevPlan& d, Pass pass, int parts, hipStream_t s, TrackState* ts = nullptr);
 hipError_t launch_render(const DevPlan& d, const uint8_t* image, int n_side, int n_len, hipStream_t s);
 hipError_t launch_extract(const struct ExArgs& x, hipStream_t s);
 
@@ -254,6 +321,7 @@ struct nhp_plan {
   size_t ws_bytes = 0;
   bool own_ws = false;
   nhp::HostTables t;
+  std::vector<int32_t> slot;  // host copy of d.slot
   nhp::DevPlan d{};
   bool has_cspace = false;
   bool has_value = false;
@@ -273,6 +341,7 @@ namespace nhp {
 // Thread-local error text of the C ABI (nhp_api.cpp).
 int set_error(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 int clear_error();
+StartTiles start_tiles(const nhp_plan* plan, int i, int j, int T);
 int upload_taps(nhp_plan* plan, int front, int rear, int half_width);
 // Checks a vehicle box; the sample offsets of all planes then take
 // taps_words() words, written by build_taps into `out`.
