@@ -9,6 +9,8 @@
 // hard afterwards.  Sample offsets come from the host (one table per plane).
 // The image and a scratch plane stay L2-resident; the volume is written
 // once.  The value volume's memory serves as the scratch volume.
+#include <string.h>
+
 #include "nhp_internal.h"
 
 namespace nhp {
@@ -179,63 +181,115 @@ __global__ __launch_bounds__(256) void render_len_batch_kernel(const RenderJob* 
 // ---- soft obstacle costs from a distance transform (Sec. VI-VII) ----
 // Squared Euclidean distance to the nearest hard pixel, split the usual
 // way: per column the squared distance to the nearest hard row, then per
-// row the minimum over columns i' of (i - i')^2 + that column's value.
+// row the minimum over columns i' of (i - i')^2 + that column's value.  The
+// table's last entry stands for every distance from len - 1 on, so neither
+// search goes further than the radius whose square reaches len - 1.  Both
+// kernels are bound by latency: 1024^2 pixels with a ramp of 24 cells take 3 +
+// 14 us (386 + 93 us with whole columns per thread and whole rows per pixel),
+// the call 30 us (832 us).
 
-constexpr uint32_t kFar = 1u << 30;  // no hard pixel in the column
+constexpr uint32_t kFar = 1u << 30;  // no hard pixel near enough in the column
+constexpr int kMaxSoftRadius = 256;  // NHP_MAX_SOFT_TABLE entries
 
-// one thread per column: two passes, down and up
-__global__ __launch_bounds__(256) void soft_cols_kernel(const uint8_t* __restrict__ image, uint32_t* __restrict__ g,
-                                                        int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// A table that travels in the kernel's arguments (no copy of its own, which
+// from pageable memory costs more than both kernels).
+struct SoftTable {
+  static constexpr int kBytes = 3072;
+  uint8_t b[kBytes];
+};
+
+// Hard pixels as bits, 32 rows of a column in a word: thread (column, word).
+// One block also lays the table down for the next kernel.  64-thread blocks:
+// the longest chain is 32 loads, so the rows of a large image are spread over
+// as many CUs as there are (1024^2: 386 us with a thread per whole column).
+__global__ __launch_bounds__(64) void soft_bits_kernel(const uint8_t* __restrict__ image, uint32_t* __restrict__ bits,
+                                                       int n, SoftTable t, int t_len, uint8_t* __restrict__ table) {
+  const int i = blockIdx.x * 64 + threadIdx.x, w = blockIdx.y;
+  if (blockIdx.x == 0 && w == 0)
+    for (int k = threadIdx.x; k < t_len; k += 64) table[k] = t.b[k];
   if (i >= n) return;
-  int last = -1;  // nearest hard row above, -1 for none
-  for (int j = 0; j < n; j++) {
-    if (image[(size_t)j * n + i] == kHard) last = j;
-    g[(size_t)j * n + i] = last < 0 ? kFar : (uint32_t)((j - last) * (j - last));
+  const uint8_t* col = image + (size_t)32 * w * n + i;
+  const int rows = n - 32 * w < 32 ? n - 32 * w : 32;  // a multiple of 8
+  uint32_t m = 0;
+  for (int r0 = 0; r0 < rows; r0 += 8) {
+#pragma unroll
+    for (int r = 0; r < 8; r++) m |= (col[(size_t)(r0 + r) * n] == kHard ? 1u : 0u) << (r0 + r);
   }
-  last = -1;  // nearest hard row below
-  for (int j = n - 1; j >= 0; j--) {
-    if (image[(size_t)j * n + i] == kHard) last = j;
-    if (last >= 0) {
-      const uint32_t d = (uint32_t)((last - j) * (last - j));
-      const size_t x = (size_t)j * n + i;
-      g[x] = d < g[x] ? d : g[x];
-    }
-  }
+  bits[(size_t)w * n + i] = m;
 }
 
-// one workgroup per row: the row of column values in LDS, a minimum over all
-// columns per pixel, then the table
-__global__ __launch_bounds__(256) void soft_rows_kernel(const uint8_t* __restrict__ image, const uint32_t* __restrict__ g,
+// One workgroup per row: the column distances of its pixels from the bit
+// words above and below, in LDS between margins of kFar, then per pixel the
+// columns outwards until no nearer pixel is possible.
+__global__ __launch_bounds__(256) void soft_rows_kernel(const uint32_t* __restrict__ bits,
                                                         const uint8_t* __restrict__ table, uint32_t len,
-                                                        uint8_t* __restrict__ out, int n) {
-  __shared__ uint32_t row[1024];
-  const int j = blockIdx.x;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) row[i] = g[(size_t)j * n + i];
-  __syncthreads();
+                                                        uint8_t* __restrict__ out, int n, int radius) {
+  __shared__ uint32_t row[1024 + 2 * kMaxSoftRadius];
+  const int j = blockIdx.x, jw = j >> 5, jb = j & 31, words = (n + 31) >> 5;
+  for (int x = threadIdx.x; x < radius; x += blockDim.x) row[x] = row[radius + n + x] = kFar;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const size_t x = (size_t)j * n + i;
-    if (image[x] == kHard) {
-      out[x] = (uint8_t)kHard;
-      continue;
+    int d = radius;  // nearest hard row, at most `radius` away
+    uint32_t m = bits[(size_t)jw * n + i];
+    const uint32_t up = m << (31 - jb), down = m >> jb;
+    if (up) d = __builtin_clz(up) < d ? __builtin_clz(up) : d;
+    if (down) d = __builtin_ctz(down) < d ? __builtin_ctz(down) : d;
+    for (int w = jw - 1; w >= 0 && j - (32 * w + 31) < d; w--) {
+      m = bits[(size_t)w * n + i];
+      if (m) {
+        const int e = j - (32 * w + 31 - __builtin_clz(m));
+        d = e < d ? e : d;
+        break;
+      }
     }
-    uint32_t best = 0xFFFFFFFFu;
-    for (int ii = 0; ii < n; ii++) {
-      const uint32_t d = (uint32_t)((i - ii) * (i - ii)) + row[ii];
+    for (int w = jw + 1; w < words && 32 * w - j < d; w++) {
+      m = bits[(size_t)w * n + i];
+      if (m) {
+        const int e = 32 * w + __builtin_ctz(m) - j;
+        d = e < d ? e : d;
+        break;
+      }
+    }
+    row[radius + i] = d < radius ? (uint32_t)(d * d) : kFar;
+  }
+  __syncthreads();
+  for (int i0 = 0; i0 < n; i0 += blockDim.x) {  // (the same rounds in every lane)
+    const int i = i0 + (int)threadIdx.x;
+    const uint32_t* at = row + radius + (i < n ? i : n - 1);
+    const uint32_t own = at[0];
+    uint32_t best = own < len - 1 ? own : len - 1;
+    for (int k = 1; __builtin_amdgcn_ballot_w64((uint32_t)(k * k) < best) != 0ull; k++) {
+      const uint32_t a = at[-k], b = at[k];
+      const uint32_t d = (uint32_t)(k * k) + (a < b ? a : b);
       best = d < best ? d : best;
     }
-    out[x] = table[best < len - 1 ? best : len - 1];
+    // a hard pixel is the only one at distance 0 (of a table of one entry, whose
+    // distances are not searched, the bit says so)
+    if (i < n) {
+      const bool hard = (bits[(size_t)jw * n + i] >> jb) & 1u;
+      out[(size_t)j * n + i] = hard ? (uint8_t)kHard : table[best];
+    }
   }
 }
 
 }  // namespace
 
-hipError_t launch_soft_costs(const uint8_t* image, uint32_t* g_scratch, const uint8_t* table, uint32_t len,
-                             uint8_t* out, int n, hipStream_t s) {
-  hipLaunchKernelGGL(soft_cols_kernel, dim3((n + 255) / 256), dim3(256), 0, s, image, g_scratch, n);
+bool soft_table_in_args(uint32_t len) { return len <= (uint32_t)SoftTable::kBytes; }
+
+hipError_t launch_soft_costs(const uint8_t* image, uint32_t* bits_scratch, const uint8_t* h_table, uint8_t* d_table,
+                             uint32_t len, uint8_t* out, int n, hipStream_t s) {
+  int radius = 0;  // the smallest whose square reaches len - 1
+  while ((uint32_t)(radius * radius) < len - 1) radius++;
+  SoftTable t;
+  int t_len = 0;
+  if (soft_table_in_args(len)) {
+    t_len = (int)len;
+    memcpy(t.b, h_table, len);
+  }
+  hipLaunchKernelGGL(soft_bits_kernel, dim3((n + 63) / 64, (n + 31) / 32), dim3(64), 0, s, image, bits_scratch, n, t,
+                     t_len, d_table);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(soft_rows_kernel, dim3(n), dim3(256), 0, s, image, g_scratch, table, len, out, n);
+  hipLaunchKernelGGL(soft_rows_kernel, dim3(n), dim3(256), 0, s, bits_scratch, d_table, len, out, n, radius);
   return hipGetLastError();
 }
 

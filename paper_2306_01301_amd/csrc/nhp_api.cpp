@@ -368,11 +368,12 @@ int soft_cost_image(nhp_plan* plan, const uint8_t* d_image, uint8_t* d_out, cons
   if (rc) return rc;
   if (!d_image || !d_out || !h_table) return fail(NHP_EINVAL, "image, out or table is NULL");
   if (table_len < 1 || table_len > NHP_MAX_SOFT_TABLE) return fail(NHP_EINVAL, "table length must be 1..%u", NHP_MAX_SOFT_TABLE);
-  // scratch: the column distances in the value volume's memory, the table in
+  // scratch: the hard pixels' bits in the value volume's memory, the table in
   // the goal-set buffer (both are rewritten before their next use)
   uint8_t* tab = reinterpret_cast<uint8_t*>(plan->d.goals);
-  HIP_CHECK(hipMemcpyAsync(tab, h_table, table_len, hipMemcpyHostToDevice, plan->stream), "table upload");
-  HIP_CHECK(nhp::launch_soft_costs(d_image, plan->d.V, tab, table_len, d_out, (int)plan->p.nx, plan->stream),
+  if (!nhp::soft_table_in_args(table_len))
+    HIP_CHECK(hipMemcpyAsync(tab, h_table, table_len, hipMemcpyHostToDevice, plan->stream), "table upload");
+  HIP_CHECK(nhp::launch_soft_costs(d_image, plan->d.V, h_table, tab, table_len, d_out, (int)plan->p.nx, plan->stream),
             "soft cost launch");
   HIP_CHECK(hipStreamSynchronize(plan->stream), "soft costs");  // the table copy is pageable
   plan->has_value = false;

@@ -261,9 +261,12 @@ struct RenderJob {
 hipError_t launch_render_batch(const RenderJob* d_jobs, int n_jobs, int total_blocks, int total_pad_rows,
                                hipStream_t s);
 int render_blocks(int N, int nt);  // workgroups of one plan's render passes
-// Soft costs of an n x n image; g_scratch: n^2 words.
-hipError_t launch_soft_costs(const uint8_t* image, uint32_t* g_scratch, const uint8_t* table, uint32_t len,
-                             uint8_t* out, int n, hipStream_t s);
+// Soft costs of an n x n image; bits_scratch: n ceil(n / 32) words; d_table:
+// len bytes.  A table that fits the kernel arguments (soft_table_in_args) is
+// taken from h_table, any other has to be in d_table already.
+bool soft_table_in_args(uint32_t len);
+hipError_t launch_soft_costs(const uint8_t* image, uint32_t* bits_scratch, const uint8_t* h_table, uint8_t* d_table,
+                             uint32_t len, uint8_t* out, int n, hipStream_t s);
 
 // ---- maneuver-count reachability (App. C) ----
 // Bit volumes: word ((T * N + j) * W + w), W = N / 32, bit t is pose
