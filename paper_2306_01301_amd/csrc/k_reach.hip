@@ -17,7 +17,7 @@
 //     words and funnels them with one alignbit.
 //   * turn curves: 32 curves per lane (one word of a row of curve origins),
 //     the curve split into S sections of P steps held in registers (the
-//     shortest sections whose lanes fit a workgroup of 256); both
+//     shortest sections that do not fill the chip over); both
 //     maneuvers of a circle family (forward and backward along it) run on the
 //     same registers; section results meet in LDS (the three passes of the
 //     Sections technique, App. D, Inserts 6-8, done in one kernel).  A lane's
@@ -132,32 +132,63 @@ struct TurnJob {
   const uint32_t* hard;
   const int32_t* offx;  // offsets of the family's curves, reduced mod N
   const int32_t* offy;
-  int N, L, W, Wp, rows, S;
+  int N, L, W, Wp, rows;
   int fwd_on, bwd_on;  // the maneuver walking up the headings / down
   int store;           // 1: write R_{m+1}; 0: AND into it
 };
 
 // Lane layout of a workgroup: section sec, row slot rr, word w:
-// thread = (sec * rows + rr) * Wp + w, Wp = W rounded up to a power of two,
-// so the Wp lanes of one (sec, rr) sit together inside one wave.
-// The most threads (sections x rows x words) per workgroup; shorter sections
-// put more lanes to work (at 128 x 128 x 512: 0.30 ms for eight cycles with
-// 256, 0.35 with 128, 0.50 with 64, 0.32 with 512).
-constexpr int kTurnThreads = 256;
+// thread = (sec * rows + rr) * Wp + w, Wp = W rounded up to a power of two and
+// G = rows * Wp a power of two of at most 64, so a wave holds the same G word
+// slots of 64 / G consecutive sections.  Threads past the last section hold
+// identity maps.
+//
+// A section maps the entering bits v to (v | D) & F, D the OR of its hard bits
+// and F its output from an unreachable entry; (D1, F1) then (D2, F2) is
+// (D1 | D2, (F1 | D2) & F2).  Once around the circle from "unreachable" at
+// section 0 gives F of them all, a fixed point, and the sections before s take
+// it to s: so one exclusive scan per direction, by shuffles inside the wave and
+// over the waves' totals through LDS.  (Walking round all the sections for each
+// took most of the kernel.  A launch at 128 x 128 x 512: 11.6 -> 8.1 us, at 512 x
+// 512 x 512, with twice the lanes: 31.0 -> 21.8 us; 50 MB of bits there, 10 us at
+// the copy rate.)
+struct BitMap {
+  uint32_t d, f;
+};
+__device__ __forceinline__ BitMap then(BitMap a, BitMap b) { return {a.d | b.d, (a.f | b.d) & b.f}; }
+
+// This wave's part of an exclusive scan over its sections (`UP`: from the
+// first, else from the last), and their composition in `all`.
+template <bool UP>
+__device__ __forceinline__ BitMap wave_scan(BitMap m, int G, BitMap& all) {
+  const int lane = threadIdx.x & 63;
+  for (int o = G; o < 64; o <<= 1) {
+    const int src = UP ? lane - o : lane + o;
+    const BitMap y = {(uint32_t)__shfl((int)m.d, src & 63, 64), (uint32_t)__shfl((int)m.f, src & 63, 64)};
+    if (UP ? src >= 0 : src < 64) m = then(y, m);
+  }
+  const int last = UP ? 64 - G + (lane & (G - 1)) : (lane & (G - 1));
+  all = {(uint32_t)__shfl((int)m.d, last, 64), (uint32_t)__shfl((int)m.f, last, 64)};
+  const int src = UP ? lane - G : lane + G;
+  const BitMap y = {(uint32_t)__shfl((int)m.d, src & 63, 64), (uint32_t)__shfl((int)m.f, src & 63, 64)};
+  return (UP ? src >= 0 : src < 64) ? y : BitMap{0u, ~0u};
+}
+
+constexpr int kTurnThreads = 1024;
 template <int P>
 __global__ __launch_bounds__(kTurnThreads) void reach_turn_kernel(TurnJob a) {
   __shared__ int32_t sox[kReachMaxL], soy[kReachMaxL];
-  __shared__ uint32_t aggD[kTurnThreads], aggF[kTurnThreads], aggB[kTurnThreads];
+  __shared__ BitMap tot[2][kTurnThreads / 64][64];
   const int tid = threadIdx.x;
   for (int t = tid; t < a.L; t += blockDim.x) {
     sox[t] = a.offx[t];
     soy[t] = a.offy[t];
   }
   __syncthreads();
-  const int N = a.N, L = a.L, W = a.W, S = a.S;
+  const int N = a.N, L = a.L, W = a.W;
   const int G = a.rows * a.Wp;
-  const int g = tid % G, sec = tid / G;
-  const int w = g % a.Wp, rr = g / a.Wp;
+  const int g = tid & (G - 1), sec = tid / G;
+  const int w = g & (a.Wp - 1), rr = g / a.Wp;
   const int yp = blockIdx.x * a.rows + rr;
   const bool live = w < W && yp < N;
   const int wl = w < W ? w : 0;  // idle lanes read valid words
@@ -180,9 +211,7 @@ __global__ __launch_bounds__(kTurnThreads) void reach_turn_kernel(TurnJob a) {
       h[k] = 0u;
     }
   }
-  // section summaries: D = OR of the hard bits (the carried bit is then
-  // replaced), F / B = the section's output from an unreachable entry,
-  // walking up / down the headings
+  // the section's map walking up (F) and down (Bk) the headings
   uint32_t D = 0, F = ~0u, Bk = ~0u;
 #pragma unroll
   for (int k = 0; k < P; k++) {
@@ -191,27 +220,26 @@ __global__ __launch_bounds__(kTurnThreads) void reach_turn_kernel(TurnJob a) {
   }
 #pragma unroll
   for (int k = P - 1; k >= 0; k--) Bk = (Bk & vi[k]) | h[k];
-  aggD[sec * G + g] = D;
-  aggF[sec * G + g] = F;
-  aggB[sec * G + g] = Bk;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = blockDim.x >> 6;
+  BitMap up_all, down_all;
+  BitMap up = wave_scan<true>({D, F}, G, up_all), down = wave_scan<false>({D, Bk}, G, down_all);
+  tot[0][wave][tid & 63] = up_all;
+  tot[1][wave][tid & 63] = down_all;
   __syncthreads();
-  // bit entering this section: once around the circle from "unreachable",
-  // starting with this section and ending with the one before it
-  uint32_t cf = ~0u, cb = ~0u;
-  if (a.fwd_on) {
-    int s2 = sec;
-    for (int t = 0; t < S; t++) {
-      cf = (cf | aggD[s2 * G + g]) & aggF[s2 * G + g];
-      s2 = (s2 + 1 == S) ? 0 : s2 + 1;
-    }
+  // the waves before this one (after it, walking down), and all of them
+  BitMap pre = {0u, ~0u}, all = {0u, ~0u}, pre2 = {0u, ~0u}, all2 = {0u, ~0u};
+  for (int x = 0; x < waves; x++) {
+    if (x == wave) pre = all;
+    all = then(all, tot[0][x][tid & 63]);
   }
-  if (a.bwd_on) {
-    int s2 = sec;
-    for (int t = 0; t < S; t++) {
-      cb = (cb | aggD[s2 * G + g]) & aggB[s2 * G + g];
-      s2 = (s2 == 0) ? S - 1 : s2 - 1;
-    }
+  for (int x = waves - 1; x >= 0; x--) {
+    if (x == wave) pre2 = all2;
+    all2 = then(all2, tot[1][x][tid & 63]);
   }
+  up = then(pre, up);
+  down = then(pre2, down);
+  // bits entering this section
+  const uint32_t cf = (all.f | up.d) & up.f, cb = (all2.f | down.d) & down.f;
   uint32_t o[P];
   uint32_t v = cf;
 #pragma unroll
@@ -281,8 +309,8 @@ struct StraightJob {
 // off-diagonal halves, quarters, ... between lane pairs, and lane r then
 // holds row 32 Y + r, word X of the transpose.  `put` receives (row, word,
 // value).  Every lane of the workgroup must call it (the stages shuffle).
-template <typename Put>
-__device__ __forceinline__ void transpose_blocks(const uint32_t* src, int W, Put put) {
+template <typename Get, typename Put>
+__device__ __forceinline__ void transpose_blocks(int W, Get get, Put put) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
   const int r = lane & 31, n_blocks = W * W, per_round = 2 * n_waves;
   const int rounds = (n_blocks + per_round - 1) / per_round;
@@ -290,7 +318,7 @@ __device__ __forceinline__ void transpose_blocks(const uint32_t* src, int W, Put
     const int blk = it * per_round + 2 * wave + (lane >> 5);
     const bool ok = blk < n_blocks;
     const int X = ok ? blk / W : 0, Y = ok ? blk % W : 0;
-    uint32_t v = ok ? src[(32 * X + r) * W + Y] : 0u;
+    uint32_t v = get(32 * X + r, Y);
     const uint32_t masks[5] = {0x0000FFFFu, 0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
 #pragma unroll
     for (int st = 0; st < 5; st++) {
@@ -306,45 +334,61 @@ __device__ __forceinline__ void transpose_blocks(const uint32_t* src, int W, Put
   }
 }
 
-constexpr int kStraightThreads = 256;
-__global__ __launch_bounds__(kStraightThreads) void reach_straight_kernel(StraightJob a) {
+// Threads of a workgroup: the walks of a large plane are long and its three
+// matrices leave room for one workgroup per CU (102 KB at N = 512), so it gets
+// all the waves a workgroup can have; small planes fit several times.  A launch
+// at 512 x 512 x 512: 166 us with 256 threads and even row pitches, 64 us now; it
+// is bound by the latency of a walk's LDS reads.
+constexpr int kStraightMaxThreads = 1024;
+int straight_threads(int N) { return N <= 160 ? 256 : (N <= 320 ? 512 : kStraightMaxThreads); }
+
+// Words of the kernel's LDS: three matrices with rows of an odd number of
+// words (so that a column of rows falls in distinct banks), the skew table, two
+// section aggregates per thread.
+__host__ __device__ constexpr int straight_pitch(int W) { return W | 1; }
+size_t straight_lds_bytes(int N, int W, int threads) {
+  return ((size_t)3 * N * straight_pitch(W) + N / 2 + 1 + 2 * threads) * 4;
+}
+
+__global__ __launch_bounds__(kStraightMaxThreads) void reach_straight_kernel(StraightJob a) {
   extern __shared__ uint32_t lds[];
-  const int N = a.N, W = a.W, NW = N * W;
+  const int N = a.N, W = a.W, NW = N * W, PW = straight_pitch(W), M = N * PW;
   uint32_t* Rp = lds;
-  uint32_t* Hp = lds + NW;
-  uint32_t* Op = lds + 2 * NW;
-  int16_t* sk = reinterpret_cast<int16_t*>(lds + 3 * NW);
+  uint32_t* Hp = lds + M;
+  uint32_t* Op = lds + 2 * M;
+  int16_t* sk = reinterpret_cast<int16_t*>(lds + 3 * M);
   const int T = blockIdx.x;
-  const size_t plane = (size_t)T * NW;
+  const uint32_t* rin = a.rin + (size_t)T * NW;
+  const uint32_t* hard = a.hard + (size_t)T * NW;
+  uint32_t* out = a.rout + (size_t)T * NW;
   const bool fam_x = a.family[T] == 0;
   const bool sf_up = a.fwd[T] > 0;
+  for (int c = threadIdx.x; c < N; c += blockDim.x) sk[c] = a.skew[(size_t)T * N + c];
   if (!fam_x) {
     for (int q = threadIdx.x; q < NW; q += blockDim.x) {
-      Rp[q] = a.rin[plane + q];
-      Hp[q] = a.hard[plane + q];
+      const int at = (q / W) * PW + q % W;
+      Rp[at] = rin[q];
+      Hp[at] = hard[q];
+      Op[at] = ~0u;
     }
   } else {
-    // row c of the LDS matrices = column c of the plane: each matrix is read
-    // into the output area first, then transposed block by block
-    for (int m = 0; m < 2; m++) {
-      const uint32_t* src = (m == 0 ? a.rin : a.hard) + plane;
-      uint32_t* dst = m == 0 ? Rp : Hp;
-      for (int q = threadIdx.x; q < NW; q += blockDim.x) Op[q] = src[q];
-      __syncthreads();
-      transpose_blocks(Op, W, [&](int row, int w, uint32_t v) { dst[row * W + w] = v; });
-      __syncthreads();
-    }
+    // row c of the LDS matrices = column c of the plane
+    transpose_blocks(W, [&](int row, int w) { return rin[row * W + w]; },
+                     [&](int row, int w, uint32_t v) { Rp[row * PW + w] = v; });
+    transpose_blocks(W, [&](int row, int w) { return hard[row * W + w]; },
+                     [&](int row, int w, uint32_t v) {
+                       Hp[row * PW + w] = v;
+                       Op[row * PW + w] = ~0u;
+                     });
   }
-  for (int q = threadIdx.x; q < NW; q += blockDim.x) Op[q] = ~0u;
-  for (int c = threadIdx.x; c < N; c += blockDim.x) sk[c] = a.skew[(size_t)T * N + c];
   __syncthreads();
   // Walkers: (group of 32 lines, direction, section of the walk).  A section
   // maps the entering bits v to (v AND A) OR B (the paper's section value and
   // distance for bits, App. D); sections compose as (A1 A2, B1 A2 | B2).
   const int walkers = 2 * W;
-  const int S = blockDim.x / walkers;  // sections per walk (at least 8: W <= 16)
+  const int S = blockDim.x / walkers;  // sections per walk
   const int len = (N + S - 1) / S;
-  uint32_t* aggA = Op + NW + N / 2 + 1;  // after the skew table
+  uint32_t* aggA = lds + 3 * M + N / 2 + 1;  // after the skew table
   uint32_t* aggB = aggA + blockDim.x;
   const int item = threadIdx.x % walkers, sec = threadIdx.x / walkers;
   const int g = item % W, dir = item / W;
@@ -359,12 +403,13 @@ __global__ __launch_bounds__(kStraightThreads) void reach_straight_kernel(Straig
     q = col >> 5;
     r = col & 31;
     q1 = (q + 1 == W) ? 0 : q + 1;
-    rb = c * W;
+    rb = c * PW;
     rw = funnel(Rp[rb + q1], Rp[rb + q], r);
     hw = funnel(Hp[rb + q1], Hp[rb + q], r);
   };
   if (on) {
     uint32_t A = ~0u, B = 0u;
+#pragma unroll 4
     for (int k = k0; k < k1; k++) {
       uint32_t rw, hw;
       int rb, q, q1, r;
@@ -378,7 +423,9 @@ __global__ __launch_bounds__(kStraightThreads) void reach_straight_kernel(Straig
   __syncthreads();
   if (on) {
     uint32_t v = ~0u;  // every line enters from the wall unreachable
+#pragma unroll 4
     for (int t = 0; t < sec; t++) v = (v & aggA[t * walkers + item]) | aggB[t * walkers + item];
+#pragma unroll 4
     for (int k = k0; k < k1; k++) {
       uint32_t rw, hw;
       int rb, q, q1, r;
@@ -392,17 +439,19 @@ __global__ __launch_bounds__(kStraightThreads) void reach_straight_kernel(Straig
     }
   }
   __syncthreads();
+  const bool store = a.store != 0;
   if (!fam_x) {
-    for (int q = threadIdx.x; q < NW; q += blockDim.x)
-      a.rout[plane + q] = a.store ? Op[q] : (a.rout[plane + q] & Op[q]);
+    for (int q = threadIdx.x; q < NW; q += blockDim.x) {
+      const uint32_t v = Op[(q / W) * PW + q % W];
+      out[q] = store ? v : (out[q] & v);
+    }
   } else {
     // transposed back on the way out
-    uint32_t* out = a.rout + plane;
-    const bool store = a.store != 0;
-    transpose_blocks(Op, W, [&](int row, int w, uint32_t v) {
-      uint32_t* dst = out + (size_t)row * W + w;
-      *dst = store ? v : (*dst & v);
-    });
+    transpose_blocks(W, [&](int row, int w) { return Op[row * PW + w]; },
+                     [&](int row, int w, uint32_t v) {
+                       uint32_t* dst = out + (size_t)row * W + w;
+                       *dst = store ? v : (*dst & v);
+                     });
   }
 }
 
@@ -410,6 +459,26 @@ template <int P>
 hipError_t launch_turn_t(const TurnJob& j, int blocks, int threads, hipStream_t s) {
   hipLaunchKernelGGL(reach_turn_kernel<P>, dim3(blocks), dim3(threads), 0, s, j);
   return hipGetLastError();
+}
+
+// Steps per section and rows of curve origins per workgroup.  Short sections
+// put more lanes to work and keep their loads few: the shortest whose lanes
+// fill the chip no more than kTurnLanes times over and fit a workgroup; then
+// rows are added up to 256 threads or a wave's 64 word slots.
+struct TurnShape {
+  int P, rows, threads;
+};
+constexpr int kTurnLanes = 256 * 1024;  // 16 waves per CU
+TurnShape turn_shape(int N, int L, int Wp) {
+  for (int P = 4; P <= 16; P <<= 1) {  // (16 always fits: at most 512 headings, 512 rows of 16 words)
+    const int S = (L + P - 1) / P;
+    if (S * Wp > kTurnThreads || S * Wp * N > kTurnLanes) continue;
+    int rows = 1;
+    while (2 * rows * Wp <= 64 && 2 * rows * Wp * S <= 256) rows <<= 1;
+    const int threads = (S * rows * Wp + 63) / 64 * 64;
+    if (threads <= kTurnThreads) return {P, rows, threads};
+  }
+  return {0, 0, 0};
 }
 
 bool has(const uint8_t* schedule, int n, int mu) {
@@ -443,12 +512,12 @@ hipError_t launch_reach_start(const ReachDev& r, uint32_t start_index, hipStream
   return hipGetLastError();
 }
 
-// The straight kernel's LDS can exceed the default dynamic limit (up to
-// 101 KB at N = 512); set once per device before any launch or capture.
+// The straight kernel's LDS can exceed the default dynamic limit (109 KB at
+// N = 512); set once per device before any launch or capture.
 hipError_t prepare_reach_kernels() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(reach_straight_kernel),
                              hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (3 * kReachMaxN * (kReachMaxN / 32) + kReachMaxN / 2 + 1 + 2 * kStraightThreads) * 4);
+                             (int)straight_lds_bytes(kReachMaxN, kReachMaxN / 32, kStraightMaxThreads));
 }
 
 hipError_t launch_reach_cycle(const ReachDev& r, const uint8_t* schedule, int n_schedule, uint32_t m, hipStream_t s) {
@@ -457,16 +526,11 @@ hipError_t launch_reach_cycle(const ReachDev& r, const uint8_t* schedule, int n_
   int store = 1;
   // turn families: left circles (LF up the headings, LB down), right
   // circles (RB up, RF down), eqs. (25)-(28)
-  // the shortest sections (most parallel lanes) whose lanes fit a workgroup
   int Wp = 1;
   while (Wp < r.W) Wp <<= 1;
-  int P = 4;
-  while (P < 32 && ((r.L + P - 1) / P) * Wp > kTurnThreads) P <<= 1;
-  const int S = (r.L + P - 1) / P;
-  if (S * Wp > kTurnThreads) return hipErrorInvalidValue;  // the plan's checks keep L and N below this
-  int rows = kTurnThreads / (Wp * S);
-  if (rows < 1) rows = 1;
-  const int threads = S * rows * Wp, blocks = (r.N + rows - 1) / rows;
+  const TurnShape t = turn_shape(r.N, r.L, Wp);
+  if (!t.P) return hipErrorInvalidValue;  // the plan's checks keep L and N within the shapes
+  const int P = t.P, rows = t.rows, threads = t.threads, blocks = (r.N + rows - 1) / rows;
   for (int fam = 0; fam < 2; fam++) {
     const int up = fam == 0 ? NHP_LF : NHP_RB, down = fam == 0 ? NHP_LB : NHP_RF;
     const bool fwd_on = has(schedule, n_schedule, up), bwd_on = has(schedule, n_schedule, down);
@@ -482,7 +546,6 @@ hipError_t launch_reach_cycle(const ReachDev& r, const uint8_t* schedule, int n_
     j.W = r.W;
     j.Wp = Wp;
     j.rows = rows;
-    j.S = S;
     j.fwd_on = fwd_on;
     j.bwd_on = bwd_on;
     j.store = store;
@@ -492,7 +555,6 @@ hipError_t launch_reach_cycle(const ReachDev& r, const uint8_t* schedule, int n_
       case 4: e = launch_turn_t<4>(j, blocks, threads, s); break;
       case 8: e = launch_turn_t<8>(j, blocks, threads, s); break;
       case 16: e = launch_turn_t<16>(j, blocks, threads, s); break;
-      case 32: e = launch_turn_t<32>(j, blocks, threads, s); break;
       default: e = hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
@@ -511,10 +573,8 @@ hipError_t launch_reach_cycle(const ReachDev& r, const uint8_t* schedule, int n_
     j.sf_on = sf;
     j.sb_on = sb;
     j.store = store;
-    // three bit matrices, the skew table (rounded up to words), two section
-    // aggregates per thread
-    const size_t lds = ((size_t)3 * r.N * r.W + r.N / 2 + 1 + 2 * kStraightThreads) * 4;
-    hipLaunchKernelGGL(reach_straight_kernel, dim3(r.L), dim3(kStraightThreads), lds, s, j);
+    const int threads = straight_threads(r.N);
+    hipLaunchKernelGGL(reach_straight_kernel, dim3(r.L), dim3(threads), straight_lds_bytes(r.N, r.W, threads), s, j);
     return hipGetLastError();
   }
   return hipSuccess;
