@@ -32,45 +32,63 @@ __device__ __forceinline__ uint8_t* padded_image(const RenderJob& r) {
   return r.side + (size_t)2 * r.N * r.N * r.nt;
 }
 
-// A thread renders 4 consecutive poses of a row (N is a multiple of 8).  A
-// sample's 4 bytes at an arbitrary column come from two aligned words
-// funnelled with one byte align, and the maximum runs on the bytes as two
-// pairs of 16-bit lanes (even and odd bytes), so a sample costs two word
-// loads for 4 poses instead of 4 byte loads.  Sample offsets are the same
-// for the whole block (one heading plane): staged in LDS, each is read into
-// a scalar register.  Samples are taken 4 at a time with independent loads
-// (the count is a run-time value).
+// A thread renders 4 W consecutive poses of a row (W words).  A sample's
+// bytes at an arbitrary column come from W + 1 aligned words funnelled with one
+// byte align per word, and the maximum runs on the bytes as two pairs of 16-bit
+// lanes whose high bytes they are: the odd bytes as the word stands, the even
+// ones shifted up by 8; the bytes below only break ties.  Sample offsets are the
+// same for the whole block (one heading plane): staged in LDS, each is read
+// into a scalar register.  Samples are taken 4 at a time with independent loads
+// (the count is a run-time value).  The kernels are bound by the vector cache's
+// data path and by this arithmetic, not by HBM, so more words per thread pay: 5
+// words loaded for 4 words of poses against 2 for 1, and addresses worked out a
+// quarter as often.
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t window4(const uint8_t* row, uint32_t a) {
-  const uint32_t* w = reinterpret_cast<const uint32_t*>(row + (a & ~3u));
-  return __builtin_amdgcn_alignbyte(w[1], w[0], a & 3u);  // bytes a .. a + 3
-}
+template <int W>
+struct __attribute__((packed, aligned(4))) WordRun {
+  uint32_t w[W + 1];
+};
 
-__device__ __forceinline__ uint32_t max4_over(const uint8_t* __restrict__ src, const int32_t* tp, int n, uint32_t i0,
-                                              int j, int N) {
+template <int W>
+__device__ __forceinline__ void max_over(const uint8_t* __restrict__ src, const int32_t* tp, int n, uint32_t i0, int j,
+                                         int N, uint32_t (&out)[W]) {
   const uint32_t pitch = 2u * (uint32_t)N;  // a padded plane is below 2^21 bytes
-  ushort2_t me = {0, 0}, mo = {0, 0};
-  auto take = [&](uint32_t win) {
-    me = __builtin_elementwise_max(me, __builtin_bit_cast(ushort2_t, win & 0x00FF00FFu));
-    mo = __builtin_elementwise_max(mo, __builtin_bit_cast(ushort2_t, (win >> 8) & 0x00FF00FFu));
+  ushort2_t me[W], mo[W];
+#pragma unroll
+  for (int e = 0; e < W; e++) me[e] = mo[e] = ushort2_t{0, 0};
+  auto load = [&](int32_t t) {
+    // (i0 is a multiple of 4, so the words start at the sample's own alignment)
+    const uint32_t at = __umul24((uint32_t)wrapn(j + tap_dy(t), N), pitch) + i0 + ((uint32_t)tap_dx(t) & ~3u);
+    return *reinterpret_cast<const WordRun<W>*>(src + at);
+  };
+  auto take = [&](const WordRun<W>& q, int32_t t) {
+#pragma unroll
+    for (int e = 0; e < W; e++) {
+      const uint32_t win = __builtin_amdgcn_alignbyte(q.w[e + 1], q.w[e], (uint32_t)t & 3u);
+      mo[e] = __builtin_elementwise_max(mo[e], __builtin_bit_cast(ushort2_t, win));
+      me[e] = __builtin_elementwise_max(me[e], __builtin_bit_cast(ushort2_t, win << 8));
+    }
   };
   int g = 0;
   for (; g + 4 <= n; g += 4) {
-    uint32_t q[4];
+    WordRun<W> q[4];
+    int32_t t[4];
 #pragma unroll
     for (int e = 0; e < 4; e++) {
-      const int32_t t = __builtin_amdgcn_readfirstlane(tp[g + e]);
-      q[e] = window4(src + __umul24((uint32_t)wrapn(j + tap_dy(t), N), pitch), i0 + (uint32_t)tap_dx(t));
+      t[e] = __builtin_amdgcn_readfirstlane(tp[g + e]);
+      q[e] = load(t[e]);
     }
 #pragma unroll
-    for (int e = 0; e < 4; e++) take(q[e]);
+    for (int e = 0; e < 4; e++) take(q[e], t[e]);
   }
   for (; g < n; g++) {
     const int32_t t = __builtin_amdgcn_readfirstlane(tp[g]);
-    take(window4(src + __umul24((uint32_t)wrapn(j + tap_dy(t), N), pitch), i0 + (uint32_t)tap_dx(t)));
+    take(load(t), t);
   }
-  return __builtin_bit_cast(uint32_t, me) | (__builtin_bit_cast(uint32_t, mo) << 8);
+#pragma unroll
+  for (int e = 0; e < W; e++)
+    out[e] = (__builtin_bit_cast(uint32_t, mo[e]) & 0xFF00FF00u) | ((__builtin_bit_cast(uint32_t, me[e]) >> 8) & 0x00FF00FFu);
 }
 
 // One render job per plan; a block covers kRenderRows rows of one plane:
@@ -104,19 +122,14 @@ __device__ __forceinline__ void pad_row(const RenderJob& r, int b) {
 // SIDE: side[T][j][i] = max over sideways samples of the walled image,
 // written to both copies of the padded row.  Otherwise B[T][j][i] = max over
 // lengthwise samples of side[T], walls forced hard.
-template <bool SIDE>
-__device__ __forceinline__ void render_rows(const RenderJob& r, int b, int32_t* tp) {
-  const int N = r.N, G = N / 4;
+template <bool SIDE, int W>
+__device__ __forceinline__ void render_rows_w(const RenderJob& r, int b, const int32_t* tp) {
+  const int N = r.N, G = N / (4 * W);
   const int groups = (N + kRenderRows - 1) / kRenderRows;
   const int T = b / groups, j0 = (b % groups) * kRenderRows;
   const int j1 = (j0 + kRenderRows) < N ? (j0 + kRenderRows) : N;
   const size_t NN = (size_t)N * N;
   const int n = SIDE ? r.n_side : r.n_len;
-  // the plane's sample offsets in LDS (global loads of them would be vector
-  // loads: the stores below might alias them)
-  const int32_t* tg = r.taps + (size_t)T * (r.n_side + r.n_len) + (SIDE ? 0 : r.n_side);
-  for (int g = threadIdx.x; g < n; g += blockDim.x) tp[g] = tg[g];
-  __syncthreads();
   const uint8_t* src = SIDE ? padded_image(r) : r.side + (size_t)T * 2 * NN;
   // the loop runs the same number of times in every lane, so the sample
   // offsets stay scalar loads (a lane past the end repeats the last group)
@@ -126,20 +139,45 @@ __device__ __forceinline__ void render_rows(const RenderJob& r, int b, int32_t* 
     const bool valid = item < total;
     const int it = valid ? item : total - 1;
     const int j = j0 + it / G;
-    const uint32_t i0 = 4u * (uint32_t)(it % G);
-    uint32_t m = max4_over(src, tp, n, i0, j, N);
-    if (SIDE) {
-      uint8_t* row = r.side + ((size_t)T * N + j) * 2 * N;
-      if (valid) {
-        *reinterpret_cast<uint32_t*>(row + i0) = m;
-        *reinterpret_cast<uint32_t*>(row + i0 + N) = m;
+    const uint32_t i0 = 4u * W * (uint32_t)(it % G);
+    uint32_t m[W];
+    max_over<W>(src, tp, n, i0, j, N, m);
+    uint8_t* row = SIDE ? r.side + ((size_t)T * N + j) * 2 * N : r.B + (size_t)T * NN + (size_t)j * N;
+    if (!SIDE) {
+      if (i0 == 0) m[0] |= kHard;
+#pragma unroll
+      for (int e = 0; e < W; e++) m[e] = j == 0 ? 0xFFFFFFFFu : m[e];
+    }
+    if (valid) {
+      uint32_t* dst = reinterpret_cast<uint32_t*>(row + i0);
+#pragma unroll
+      for (int e = 0; e < W; e++) dst[e] = m[e];
+      if (SIDE) {
+        dst = reinterpret_cast<uint32_t*>(row + i0 + N);
+#pragma unroll
+        for (int e = 0; e < W; e++) dst[e] = m[e];
       }
-    } else {
-      if (j == 0) m = 0xFFFFFFFFu;
-      if (i0 == 0) m |= kHard;
-      if (valid) *reinterpret_cast<uint32_t*>(r.B + (size_t)T * NN + (size_t)j * N + i0) = m;
     }
   }
+}
+
+// Words per thread: as many as leave every thread of a block an item (16 rows
+// of N poses) and divide the row.
+template <bool SIDE>
+__device__ __forceinline__ void render_rows(const RenderJob& r, int b, int32_t* tp) {
+  const int N = r.N, groups = (N + kRenderRows - 1) / kRenderRows, T = b / groups;
+  const int n = SIDE ? r.n_side : r.n_len;
+  // the plane's sample offsets in LDS (global loads of them would be vector
+  // loads: the stores below might alias them)
+  const int32_t* tg = r.taps + (size_t)T * (r.n_side + r.n_len) + (SIDE ? 0 : r.n_side);
+  for (int g = threadIdx.x; g < n; g += blockDim.x) tp[g] = tg[g];
+  __syncthreads();
+  if (N >= 256 && N % 16 == 0)
+    render_rows_w<SIDE, 4>(r, b, tp);
+  else if (N >= 128)
+    render_rows_w<SIDE, 2>(r, b, tp);
+  else
+    render_rows_w<SIDE, 1>(r, b, tp);
 }
 
 __global__ __launch_bounds__(256) void pad_image_kernel(RenderJob r) { pad_row(r, blockIdx.x); }

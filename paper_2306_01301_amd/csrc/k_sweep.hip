@@ -1152,7 +1152,7 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
     // owned cells run between two columns, where B(c) - bmin passes the row
     // (first line) and the row minus t_lim (past the last line), and those
     // lie inside the chunk only for the first brange rows after band row 0
-    // and after band row t_lim.  One lane of the last wave per such (row,
+    // and after band row t_lim.  One lane of the last waves per such (row,
     // edge) finds the column from the first-column table (here, so that the
     // read overlaps the scan) and, when it falls inside a group, writes that
     // group's owned cells one by one after the whole groups are stored; the
@@ -1161,10 +1161,10 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
     int pg_rho = 0;         // its band row
     uint32_t pg_rec = 0;    // its record index
     uint32_t pg_own = 0;    // owned cells of the group, bit m for memory column gm + m
-    if (wave == NW - 1) {
-      const int r = lane & 31;
-      if (r < brange) {  // uniform per half-wave
-        const bool last = lane >= 32;
+    if (const int e = tid - (NT - 2 * Q); e >= 0) {  // (whole waves)
+      const int r = e % Q;
+      if (r < brange) {
+        const bool last = e >= Q;
         const int rho = last ? t_lim + r : r;
         // |B - B(0)| at the first column past the edge, in memory order
         const int v = last ? (incr ? r + 1 + bmin - b0 : b0 - (r + bmin))
@@ -1785,6 +1785,26 @@ hipError_t launch_force_walls(const DevPlan& d, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Columns per chunk of a band launch.  A chunk costs the latency of its loads
+// (one chunk ahead) and three barriers whatever its width, so a launch of few
+// tiles, at most about one per CU at a time, takes half as many chunks of 64
+// columns with 8 waves: 34 tiles (64^2 x 64) 8.1 -> 6.4 us, 152 (200^2 x 72)
+// 18.3 -> 15.0, 396 (384^2 x 128) 33.8 -> 28.2.  With more tiles than that the
+// narrow chunks of several tiles per CU hide each other's latency: 520 tiles
+// (256^2 x 256) 26.9 us against 29.9, 2064 (512^3) 105 against 131.  (Chunks of
+// 128 columns with 16 waves: 8.8, 16.0, 41.5 and 42.3 us on the first four.)
+constexpr int kFewBandTiles = 448;
+bool wide_chunks(const SweepJob& j) { return j.N >= 64 && j.blocks <= kFewBandTiles; }
+
+template <int Q, int NT, int BUFS>
+void launch_band(const SweepJob& j, hipStream_t s) {
+  const dim3 grid(xmajor_grid(j.blocks, kXBandGridPerCU)), block(NT);
+  if (j.tr.mode != kTrackOff)
+    hipLaunchKernelGGL((xmajor_band_kernel<Q, NT, BUFS, true>), grid, block, 0, s, j);
+  else
+    hipLaunchKernelGGL((xmajor_band_kernel<Q, NT, BUFS, false>), grid, block, 0, s, j);
+}
+
 // Tracking costs a row launch about 8 us (finding the active tiles, stamping
 // the last one) and a pass with every tile active about 8 % more, and saves
 // the tiles that no change has reached.  Volumes of at least 2^26 poses gain:
@@ -1816,15 +1836,12 @@ hipError_t launch_sweep_part(const DevPlan& d, Pass pass, int parts, hipStream_t
     const bool wide = xmajor_wide(xmaj.N);
     const bool one = knob(NHP_KNOB_XMAJOR_BUFFERS, wide ? XB_BUFS_BUILTIN : XBUFS_BUILTIN) == 1;
     if (wide) {
-      const dim3 grid(xmajor_grid(xmaj.blocks, kXBandGridPerCU)), block(XBNT);
-      if (xmaj.tr.mode != kTrackOff && one)
-        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 1, true>), grid, block, 0, s, xmaj);
-      else if (xmaj.tr.mode != kTrackOff)
-        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 2, true>), grid, block, 0, s, xmaj);
+      if (one && wide_chunks(xmaj))
+        launch_band<2 * XBQ, 2 * XBNT, 1>(xmaj, s);
       else if (one)
-        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 1, false>), grid, block, 0, s, xmaj);
+        launch_band<XBQ, XBNT, 1>(xmaj, s);
       else
-        hipLaunchKernelGGL((xmajor_band_kernel<XBQ, XBNT, 2, false>), grid, block, 0, s, xmaj);
+        launch_band<XBQ, XBNT, 2>(xmaj, s);
     } else {
       const dim3 grid(xmajor_grid(xmaj.blocks, 6)), block(XNT);
       if (one)

@@ -1,5 +1,5 @@
-"""Launch shapes of the reachability and soft-cost kernels at their edges,
-against the oracle, bit for bit."""
+"""Launch shapes of the kernels at their edges, against the oracle, bit for
+bit."""
 import numpy as np
 import pytest
 import torch
@@ -61,4 +61,43 @@ def test_soft_cost_tables_match_oracle(n, length):
     table = rng.integers(0, 255, length).astype(np.uint8)
     p = P.planner_for(scenes.free_space(n, 8, 2.0, 1))
     assert np.array_equal(p.soft_costs(_dev(img), table).cpu().numpy(), oracle.soft_costs(img, table))
+    p.close()
+
+
+# words per thread of the rendering kernels: sides on both sides of each rule
+# and of each divisibility, boxes with sample counts around the unrolled four,
+# codes that differ in every byte
+@pytest.mark.parametrize("n,nt,box", [(16, 8, (0, 0, 0)), (120, 8, (3, 1, 1)), (128, 16, (2, 1, 2)), (136, 8, (4, 0, 1)),
+                                      (248, 8, (9, 3, 4)), (256, 24, (40, 11, 9)), (264, 16, (5, 2, 1)),
+                                      (272, 8, (255, 0, 255)), (512, 8, (7, 2, 2)), (1000, 8, (30, 7, 9))])
+def test_render_shapes_match_oracle(n, nt, box):
+    print("render %d x %d %s" % (n, nt, box), flush=True)
+    rng = np.random.default_rng(n + nt)
+    sc = scenes.free_space(n, nt, 2.0, 1, half_cell=1)
+    img = rng.integers(0, 256, (n, n)).astype(np.uint8)
+    img[rng.random((n, n)) < 0.9] = 0
+    p = P.planner_for(sc)
+    p.render(_dev(img), box)
+    assert np.array_equal(p.cspace_numpy(), oracle.render(problem_of(sc), img, *box))
+    p.close()
+
+
+# straight launches of few tiles (64-column chunks): sides that leave chunks of
+# 8 to 56 columns, one tile per row and several, and the first side above
+@pytest.mark.parametrize("n,nt", [(64, 8), (72, 24), (120, 16), (136, 16), (248, 8), (264, 40), (512, 96), (448, 120), (448, 136)])
+def test_straight_chunks_match_oracle(n, nt):
+    rng = np.random.default_rng(n * 3 + nt)
+    sc = scenes.random_small(n + nt, n=n, nt=nt, R=3.0, n_rect=max(2, n // 8)).with_(vehicle=(3, 1, 1))
+    prob = problem_of(sc)
+    B = oracle.render(prob, sc.image, *sc.vehicle)
+    p = P.planner_for(sc)
+    p.set_cspace(_dev(B))
+    for mu in (oracle.SF, oracle.SB):
+        print("straight %d x %d mu=%d" % (n, nt, mu), flush=True)
+        V = rng.integers(0, 1 << 24, size=B.shape, dtype=np.uint64).astype(np.uint32)
+        V[rng.random(B.shape) < 0.3] = 0xFFFFFFFF
+        p.value.copy_(_dev(V.view(np.int32)))
+        p.sweep_one(mu)
+        oracle.sweep(prob, mu, B, V)
+        assert np.array_equal(p.value_numpy(), V)
     p.close()
