@@ -53,7 +53,7 @@ def kernel_kind(first: int, second: int) -> str:
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for name in ("k_sweep.hip", "nhp_internal.h"):
+    for name in ("sweep_tiles.h", "k_sweep.hip", "nhp_internal.h"):
         with open(os.path.join(ROOT, "paper_2306_01301_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

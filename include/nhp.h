@@ -259,7 +259,10 @@ int extract_path_set(nhp_plan* plan, const uint32_t* goals_ijt, const uint32_t* 
                      uint32_t* goal_value_q10, uint32_t* score_q10);
 
 /* Device pointers of the plan's value and obstacle volumes (for parity
- * checks and checkpoints; owned by the plan).  Either output may be NULL. */
+ * checks and checkpoints; owned by the plan).  Either output may be NULL.
+ * The caller may write the volumes between calls: a plan whose pointers have
+ * been asked for has sweep_resume and batch_advance visit every tile again
+ * (others go on from what their last call left). */
 int plan_device_ptrs(const nhp_plan* plan, uint32_t** d_value, uint8_t** d_cspace);
 
 /* Copies the host tables out (each host array may be NULL):
@@ -307,11 +310,13 @@ int batch_init(nhp_batch* batch, nhp_plan* const* plans, const uint32_t* starts_
 int batch_step(nhp_batch* batch, nhp_plan* const* plans, const uint32_t* steps, uint32_t n);
 
 /* Several ticks at once: plan k runs its sweeps steps[k] .. steps[k] +
- * counts[k] - 1 (counts[k] = 0: none).  A call whose launches repeat those
- * of an earlier call on this batch (the same plans at the same points of
- * their schedules, under the same knobs) is captured into a HIP graph the
- * second time and replayed after that; the batch keeps up to 16 such graphs,
- * each with its own device copy of its job table.  Consecutive turn sweeps on the same
+ * counts[k] - 1 (counts[k] = 0: none).  Calls over at least 2^24 poses
+ * (plans with counts[k] > 0, all of side 32 or more) visit only the tiles
+ * that changes have reached.  A smaller call whose launches repeat those of
+ * an earlier call on this batch (the same plans at the same points of their
+ * schedules, under the same knobs) is captured into a HIP graph the second
+ * time and replayed after that; the batch keeps up to 16 such graphs, each
+ * with its own device copy of its job table.  Consecutive turn sweeps on the same
  * circles in opposite directions (RB then RF, LB then LF, and the reverse
  * orders) share one pass over the volume, with the same result as two
  * batch_step calls; pass t of every plan goes into shared launches (at most
@@ -322,8 +327,7 @@ int batch_advance(nhp_batch* batch, nhp_plan* const* plans, const uint32_t* step
 /* batch_init, then one batch_advance per cycle (the plans with cycles
  * left, each with the passes sweep_n_turns runs: a cycle's last sweep shares
  * a pass with the next cycle's first when they fuse): plan k ends with
- * n_cycles[k] cycles, as sweep_n_turns would leave it.  Cycles that repeat
- * the launches of an earlier one replay them from a captured graph. */
+ * n_cycles[k] cycles, as sweep_n_turns would leave it. */
 int batch_sweep(nhp_batch* batch, nhp_plan* const* plans, const uint32_t* starts_ijt,
                 const uint32_t* n_cycles, uint32_t n);
 

@@ -166,6 +166,24 @@ nhp::StartTiles nhp::start_tiles(const nhp_plan* plan, int i, int j, int T) {
   return out;
 }
 
+// After init: the stamps say where the starts are, and no pass has run.
+void nhp::track_restart(nhp_plan* plan) {
+  plan->ts = TrackState{};
+  plan->ts_valid = true;
+}
+
+// Before a tracked run: where the stamps do not describe the volume (or the
+// pass numbers run out), all are cleared and the first pass of every maneuver
+// visits all tiles.
+int nhp::track_plan(nhp_plan* plan, hipStream_t stream) {
+  if (plan->ts_valid && plan->ts.pass < (1u << 30)) return NHP_OK;
+  HIP_CHECK(launch_clear_stamps(plan->d, stream), "stamp launch");
+  plan->ts = TrackState{};
+  for (uint32_t& q : plan->ts.last) q = kTrackStale;
+  plan->ts_valid = true;
+  return NHP_OK;
+}
+
 static int finish_extract(nhp_plan* plan, nhp_step* h_steps, uint32_t cap, uint32_t* n_steps, uint32_t* best_ijt,
                           uint32_t* best_index, uint32_t* goal_value_q10, uint32_t* score_q10);
 
@@ -436,10 +454,16 @@ static hipGraphExec_t capture_passes(nhp_plan* plan, const std::vector<nhp::Pass
 // capturing and instantiating costs more than the launches it saves on a
 // plan that is swept only once.
 // A plan whose sweeps are tracked launches its kernels directly: their
-// arguments carry the pass numbers.  ts: the run's tracking state (the volume
-// is the one the stamps describe), nullptr: untracked.
-static int run_cycles(nhp_plan* plan, uint32_t n_cycles, nhp::TrackState* ts) {
+// arguments carry the pass numbers.
+static int run_cycles(nhp_plan* plan, uint32_t n_cycles) {
   const bool pairs = nhp::can_fuse(plan->d);
+  nhp::TrackState* ts = nullptr;
+  if (nhp::track_sweeps(plan->d) && (plan->ts_valid || n_cycles > 1)) {
+    int rc = nhp::track_plan(plan, plan->stream);
+    if (rc) return rc;
+    ts = &plan->ts;
+  }
+  plan->ts_valid = false;  // (until all passes are launched)
   const bool graphs = !ts && n_cycles > 1 && plan->multi_cycle_runs++ > 0;
   bool skip = false;
   std::vector<nhp::Pass> passes;
@@ -456,6 +480,7 @@ static int run_cycles(nhp_plan* plan, uint32_t n_cycles, nhp::TrackState* ts) {
     }
     skip = consumed;
   }
+  plan->ts_valid = ts != nullptr || n_cycles == 0;
   return NHP_OK;
 }
 
@@ -476,8 +501,8 @@ int sweep_n_turns(nhp_plan* plan, uint32_t si, uint32_t sj, uint32_t st, uint32_
   plan->start[1] = sj;
   plan->start[2] = st;
   plan->has_value = true;
-  nhp::TrackState ts;
-  return (rc = run_cycles(plan, n_cycles, nhp::track_sweeps(plan->d) ? &ts : nullptr)) ? rc : ok();
+  nhp::track_restart(plan);
+  return (rc = run_cycles(plan, n_cycles)) ? rc : ok();
 }
 
 int sweep_from_set(nhp_plan* plan, const nhp_start* h_starts, uint32_t n_starts, uint32_t n_cycles) {
@@ -511,21 +536,16 @@ int sweep_from_set(nhp_plan* plan, const nhp_start* h_starts, uint32_t n_starts,
   plan->start[1] = h_starts[0].j;
   plan->start[2] = h_starts[0].T;
   plan->has_value = true;
-  nhp::TrackState ts;
-  return (rc = run_cycles(plan, n_cycles, nhp::track_sweeps(plan->d) ? &ts : nullptr)) ? rc : ok();
+  nhp::track_restart(plan);
+  return (rc = run_cycles(plan, n_cycles)) ? rc : ok();
 }
 
 int sweep_resume(nhp_plan* plan, uint32_t n_more_cycles) {
   int rc = check_plan(plan);
   if (rc) return rc;
   if (!plan->has_value) return fail(NHP_ESTATE, "sweep_resume before sweep_n_turns");
-  // the caller may have written the value volume since the last sweep: the
-  // first pass of every maneuver visits all tiles
-  nhp::TrackState ts;
-  for (uint32_t& q : ts.last) q = nhp::kTrackStale;
-  const bool track = n_more_cycles > 1 && nhp::track_sweeps(plan->d);
-  if (track) HIP_CHECK(nhp::launch_clear_stamps(plan->d, plan->stream), "stamp launch");
-  return (rc = run_cycles(plan, n_more_cycles, track ? &ts : nullptr)) ? rc : ok();
+  if (plan->exposed) plan->ts_valid = false;
+  return (rc = run_cycles(plan, n_more_cycles)) ? rc : ok();
 }
 
 int sweep_pass(nhp_plan* plan, int32_t first, int32_t second) {
@@ -533,6 +553,7 @@ int sweep_pass(nhp_plan* plan, int32_t first, int32_t second) {
   if (rc) return rc;
   if (!plan->has_cspace) return fail(NHP_ESTATE, "sweep_pass before render_cspace/plan_set_cspace");
   if (first < 0 || first > 5 || second < -1 || second > 5) return fail(NHP_EINVAL, "maneuvers must be 0..5 (second: -1 for none)");
+  plan->ts_valid = false;
   HIP_CHECK(nhp::launch_sweep(plan->d, nhp::Pass{(int8_t)first, (int8_t)second}, plan->stream), "sweep launch");
   return ok();
 }
@@ -543,6 +564,7 @@ int sweep_straight_family(nhp_plan* plan, uint32_t maneuver, uint32_t family) {
   if (!plan->has_cspace) return fail(NHP_ESTATE, "sweep_straight_family before render_cspace/plan_set_cspace");
   if (maneuver != NHP_SF && maneuver != NHP_SB) return fail(NHP_EINVAL, "maneuver must be NHP_SF or NHP_SB");
   if (family > 1) return fail(NHP_EINVAL, "family must be 0 or 1");
+  plan->ts_valid = false;
   HIP_CHECK(nhp::launch_sweep_part(plan->d, nhp::Pass{(int8_t)maneuver, (int8_t)-1}, family ? 1 : 2, plan->stream),
             "sweep launch");
   return ok();
@@ -570,6 +592,7 @@ int sweep_one(nhp_plan* plan, uint32_t maneuver) {
   if (rc) return rc;
   if (!plan->has_cspace) return fail(NHP_ESTATE, "sweep_one before render_cspace/plan_set_cspace");
   if (maneuver > 5) return fail(NHP_EINVAL, "maneuver must be 0..5");
+  plan->ts_valid = false;
   HIP_CHECK(nhp::launch_sweep(plan->d, nhp::Pass{(int8_t)maneuver, (int8_t)-1}, plan->stream), "sweep launch");
   return ok();
 }
@@ -754,6 +777,8 @@ int extract_path_set(nhp_plan* plan, const uint32_t* goals_ijt, const uint32_t* 
 int plan_device_ptrs(const nhp_plan* plan, uint32_t** d_value, uint8_t** d_cspace) {
   int rc = check_plan(plan);
   if (rc) return rc;
+  // (the plan is the caller's own, handed out as nhp_plan*)
+  if (d_value || d_cspace) const_cast<nhp_plan*>(plan)->exposed = true;
   if (d_value) *d_value = plan->d.V;
   if (d_cspace) *d_cspace = plan->d.B;
   return ok();

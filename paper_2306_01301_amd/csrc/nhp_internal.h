@@ -107,7 +107,9 @@ __host__ __device__ inline StampLayout stamp_layout(int nx, int nt) {
 }
 
 // Pass numbers of a tracked run of sweeps: the pass each maneuver last ran
-// in (0: not yet; kTrackStale: its next pass visits every tile).
+// in (0: not yet; kTrackStale: its next pass visits every tile).  A plan's
+// state says how its stamps and its volume stand to each other (nhp_plan::ts,
+// ts_valid).
 constexpr uint32_t kTrackStale = 0xFFFFFFFFu;
 struct TrackState {
   uint32_t pass = 0;
@@ -182,12 +184,17 @@ int set_section_steps(int len, int P);
 // get_knob returns the value (0 = built-in) or -1.
 constexpr int kKnobs = 4;
 int set_knob(int knob, int value);
+int knob(int knob, int builtin);                  // the knob's value, or the built-in one
+int row_grid(int blocks, int waves, int P);       // workgroups of a row launch
+int xmajor_grid(int blocks, int per_cu);          // and of an x-major launch
 int get_knob(int knob);
 // ts: the tracked run the pass belongs to (its pass number and the
 // maneuvers' last passes are moved on), or nullptr.
 int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj, TrackState* ts = nullptr);
-// Whether a plan's sweeps are worth tracking (see k_sweep.hip).
+// Whether a plan's sweeps are worth tracking on their own (see k_sweep.hip),
+// and whether they can be tracked at all.
 bool track_sweeps(const DevPlan& d);
+bool trackable(const DevPlan& d);
 // Whether x-major jobs of grid side N take the 4-column-load kernel (batched
 // x-major launches group their jobs by it and pass it as `pow2`).
 bool xmajor_wide(int N);
@@ -195,8 +202,15 @@ int xmajor_lines(int N);  // lines per x-major tile
 // Row jobs of one launch share P, fused, guard (= L % P != 0) and their
 // wave count (the workgroup size is 64 waves threads); x-major jobs of one
 // launch share xmajor_wide(N), passed as pow2.
+// lists: tracked jobs (every job's tr.mode is kTrackSkip or kTrackAll): the
+// tiles to visit are listed first.
+struct TileLists {
+  uint2* list;         // (tile, job) of every tile to visit; room for the launch's blocks
+  uint32_t* counters;  // two: the launches take turns, each clears the other's
+  int which;
+};
 hipError_t launch_sweep_batch(const SweepJob* d_jobs, int n_jobs, int total_blocks, int P, bool fused, bool guard,
-                              bool pow2, bool xmajor, int waves, hipStream_t s);
+                              bool pow2, bool xmajor, int waves, const TileLists* lists, hipStream_t s);
 hipError_t launch_init_batch(const InitJob* d_jobs, int n_jobs, size_t max_n4, hipStream_t s);
 
 // extract buffer layout (uint32 words)
@@ -328,6 +342,11 @@ struct nhp_plan {
   nhp::DevPlan d{};
   bool has_cspace = false;
   bool has_value = false;
+  // The stamps describe the value volume as the passes of `ts` left it.
+  // exposed: the caller has the volumes' addresses, so they may have been
+  // written whenever a call begins that goes on from them.
+  nhp::TrackState ts;
+  bool ts_valid = false, exposed = false;
   uint32_t start[3] = {0, 0, 0};
   int front = -1, rear = -1, half_width = -1;  // box of the last render (sample offsets cached)
   // One cycle of the schedule, captured once and replayed per cycle; indexed
@@ -345,6 +364,8 @@ namespace nhp {
 int set_error(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 int clear_error();
 StartTiles start_tiles(const nhp_plan* plan, int i, int j, int T);
+void track_restart(nhp_plan* plan);
+int track_plan(nhp_plan* plan, hipStream_t stream);
 int upload_taps(nhp_plan* plan, int front, int rear, int half_width);
 // Checks a vehicle box; the sample offsets of all planes then take
 // taps_words() words, written by build_taps into `out`.

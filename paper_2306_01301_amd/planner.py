@@ -258,24 +258,31 @@ class Planner:
         with torch.cuda.device(self.device):
             _check(L.plan_create(ctypes.byref(self.params), ctypes.c_void_p(self.ws.data_ptr()), nbytes,
                                  ctypes.c_void_p(self.stream.cuda_stream), ctypes.byref(self._plan)), "plan_create")
-        v, b = ctypes.c_void_p(), ctypes.c_void_p()
-        _check(L.plan_device_ptrs(self._plan, ctypes.byref(v), ctypes.byref(b)), "plan_device_ptrs")
-        nr = self.nx * self.nx * self.nt
-        base = self.ws.data_ptr()
-        self._v_off, self._b_off = v.value - base, b.value - base
-        self.n_poses = nr
+        self.n_poses = self.nx * self.nx * self.nt
+        self._offsets = None
 
     # ---- views of the plan's device volumes (no copies) ----
+    def _volume_offsets(self) -> Tuple[int, int]:
+        """Byte offsets of V and of the codes in the workspace, asked for when
+        a view is: from then on the library takes them to be written between
+        calls."""
+        if self._offsets is None:
+            v, b = ctypes.c_void_p(), ctypes.c_void_p()
+            _check(lib().plan_device_ptrs(self._plan, ctypes.byref(v), ctypes.byref(b)), "plan_device_ptrs")
+            base = self.ws.data_ptr()
+            self._offsets = (v.value - base, b.value - base)
+        return self._offsets
+
     @property
     def value(self) -> torch.Tensor:
         """V as an int32 view [theta, y, x] (reinterpret as uint32 on the host)."""
-        nr = self.n_poses
-        return self.ws[self._v_off:self._v_off + 4 * nr].view(torch.int32).view(self.nt, self.nx, self.nx)
+        nr, o = self.n_poses, self._volume_offsets()[0]
+        return self.ws[o:o + 4 * nr].view(torch.int32).view(self.nt, self.nx, self.nx)
 
     @property
     def cspace(self) -> torch.Tensor:
-        nr = self.n_poses
-        return self.ws[self._b_off:self._b_off + nr].view(self.nt, self.nx, self.nx)
+        nr, o = self.n_poses, self._volume_offsets()[1]
+        return self.ws[o:o + nr].view(self.nt, self.nx, self.nx)
 
     def value_numpy(self) -> np.ndarray:
         self.stream.synchronize()

@@ -130,7 +130,7 @@ def traffic(fetch_dir: str, write_dir: str, workload: str, copy_bytes: int, comm
         per[kind].append((fb, wb))
         names[kind].add(name)
     h = hashlib.sha256()
-    for name in ("k_sweep.hip", "nhp_internal.h"):
+    for name in ("sweep_tiles.h", "k_sweep.hip", "nhp_internal.h"):
         with open(os.path.join(ROOT, "paper_2306_01301_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return {

@@ -30,7 +30,7 @@ def _scene(n, nt, seed, schedule):
     img = np.where(img == 255, 255, rng.integers(0, 3, img.shape) * 40).astype(np.uint8)
     i, j = n // 3, n - n // 3
     img[j - 12:j + 13, i - 12:i + 13] = 0
-    return scenes.Scene("t", n, nt, 9.0, img, (3, 1, 1), (i, j, nt // 5), (0, 0, 0), 0, ct=scenes.uniform_ct(18),
+    return scenes.Scene("t", n, nt, 9.0, img, (3, 1, 1) if n >= 32 else (0, 0, 0), (i, j, nt // 5), (0, 0, 0), 0, ct=scenes.uniform_ct(18),
                         gear=scenes.reverse_gear(320), schedule=schedule)
 
 
@@ -87,3 +87,115 @@ def test_tracked_start_set_equals_every_pass_in_full(n, nt):
     p.sweep_from_set(starts, 3)
     _same(p, want, "start set")
     p.close()
+
+
+def _mixed_plans(extra=()):
+    """Plans of every section size and both grid kinds, over 2^24 poses together."""
+    scs = [_scene(n, nt, 3 * n + nt, sched) for n, nt, sched in
+           ((128, 128, FULL), (200, 72, FULL), (256, 256, FULL), (64, 512, (LF, SF, RF)), (384, 128, FULL),
+            (72, 1000, (RB, RF, SF)), (96, 64, FULL)) + tuple(extra)]
+    ps = [P.planner_for(sc) for sc in scs]
+    for p, sc in zip(ps, scs):
+        p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+    return scs, ps
+
+
+def _in_full(scs, cycles, edit=None):
+    """The volumes after every pass run by itself (edit: (after cycles, change))."""
+    out = []
+    for sc, n in zip(scs, cycles):
+        p = P.planner_for(sc)
+        p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+        p.sweep(sc.start, 0)
+        if edit:
+            _passes(p, sc.schedule, edit[0])
+            edit[1](p)
+            for a, b in P.schedule_passes(sc.schedule, edit[0] * len(sc.schedule), n * len(sc.schedule)):
+                p.sweep_pass(a, b)
+        else:
+            _passes(p, sc.schedule, n)
+        out.append(p.value.clone())
+        p.close()
+    return out
+
+
+@pytest.mark.parametrize("extra", [(), ((16, 24, FULL),)])  # (a side under 32 leaves all of them untracked)
+def test_tracked_batch_sweep_equals_every_pass_in_full(extra):
+    scs, ps = _mixed_plans(extra)
+    cycles = [3 + k % 4 for k in range(len(scs))]
+    want = _in_full(scs, cycles)
+    b = P.Batch(len(scs))
+    for _ in range(2):
+        b.sweep(ps, [sc.start for sc in scs], cycles)
+    for p, w, sc in zip(ps, want, scs):
+        _same(p, w, (sc.nx, sc.nt))
+    b.close()
+    for p in ps:
+        p.close()
+
+
+def test_tracked_batch_goes_on_over_calls():
+    """Calls that go on from the last one's volumes, some plans sitting one
+    out, then resumed by themselves and in the batch again."""
+    scs, ps = _mixed_plans()
+    b = P.Batch(len(scs))
+    b.init(ps, [sc.start for sc in scs])
+    done = [0] * len(scs)
+    for call in range(5):
+        counts = [0 if (k + call) % 5 == 0 else len(sc.schedule) * (1 + (k + call) % 2) for k, sc in enumerate(scs)]
+        b.advance(ps, done, counts)
+        done = [d + c for d, c in zip(done, counts)]
+    torch.cuda.synchronize()
+    for p in ps:
+        p.resume(2)
+    torch.cuda.synchronize()
+    b.advance(ps, [0] * len(ps), [2 * len(sc.schedule) for sc in scs])
+    cycles = [d // len(sc.schedule) + 4 for d, sc in zip(done, scs)]
+    # (plain passes pair turns across cycles as one run does: the volumes are those of the sweeps one by one)
+    want = _in_full(scs, cycles)
+    for p, w, sc in zip(ps, want, scs):
+        _same(p, w, (sc.nx, sc.nt))
+    b.close()
+    for p in ps:
+        p.close()
+
+
+def test_volumes_written_between_batch_calls():
+    """A caller that has a volume's address may write it between two calls."""
+    def change(p):
+        p.value[2, 3:40, 5:50] = 1 << 18
+
+    scs, ps = _mixed_plans()
+    want = _in_full(scs, [3] * len(scs), (2, change))
+    b = P.Batch(len(scs))
+    b.init(ps, [sc.start for sc in scs])
+    b.advance(ps, [0] * len(ps), [2 * len(sc.schedule) for sc in scs])
+    for p in ps:
+        change(p)
+    b.advance(ps, [2 * len(sc.schedule) for sc in scs], [3 * len(sc.schedule) for sc in scs])
+    for p, w, sc in zip(ps, want, scs):
+        _same(p, w, (sc.nx, sc.nt))
+    b.close()
+    for p in ps:
+        p.close()
+
+
+def test_tracked_resume_of_a_volume_nobody_has_seen():
+    sc = _scene(512, 256, 9, FULL)
+    want = _in_full([sc], [5])[0]
+    p = P.planner_for(sc)
+    p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+    p.sweep(sc.start, 2)
+    p.resume(1)
+    p.resume(2)
+    _same(p, want, "resume")
+    # a pass run by itself in between is not tracked
+    q = P.planner_for(sc)
+    q.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+    q.sweep(sc.start, 2)
+    for mu in FULL:
+        q.sweep_one(mu)
+    q.resume(2)
+    _same(q, want, "resume after single passes")
+    p.close()
+    q.close()
