@@ -1,7 +1,7 @@
 // k_extract.hip -- goal search (Sec. IX) and back-tracking (Sec. X, eq. 32)
 // in one kernel, so the value volume never leaves the device and the serial
 // back-tracking loop pays no launch per step.  A single plan uses one
-// workgroup per scheduled maneuver, joined by a grid-wide barrier per step;
+// workgroup per scheduled maneuver, which exchange their best in every step;
 // a batch uses one workgroup per plan.
 //
 // Back-tracking step ("Bellman iteration in reverse"): for every scheduled
@@ -63,22 +63,12 @@ __device__ void block_scan_sat(uint32_t (&x)[M], uint32_t (*red)[NW]) {
     for (int m = 0; m < M; m++) red[m][wave] = x[m];
   }
   __syncthreads();
-  if (wave == 0) {
 #pragma unroll
-    for (int m = 0; m < M; m++) {
-      uint32_t t = lane < NW ? red[m][lane] : 0u;
+  for (int m = 0; m < M; m++) {
+    uint32_t before = 0;
 #pragma unroll
-      for (int o = 1; o < NW; o <<= 1) {
-        const uint32_t y = __shfl_up(t, o, 64);
-        if (lane >= o) t = sadd(t, y);
-      }
-      if (lane < NW) red[m][lane] = t;
-    }
-  }
-  __syncthreads();
-  if (wave > 0) {
-#pragma unroll
-    for (int m = 0; m < M; m++) x[m] = sadd(x[m], red[m][wave - 1]);
+    for (int w = 0; w < NW - 1; w++) before = sadd(before, w < wave ? red[m][w] : 0u);
+    x[m] = sadd(x[m], before);
   }
   __syncthreads();
 }
@@ -98,7 +88,6 @@ __device__ uint64_t block_min_u64(uint64_t x, uint64_t* red) {
   __syncthreads();
   return r;
 }
-
 
 __device__ __forceinline__ size_t pose_index(int N, int i, int j, int T) {
   return ((size_t)T * N + j) * N + i;
@@ -221,53 +210,30 @@ __global__ __launch_bounds__(kThreads) void seed_kernel(DevPlan d) {
   }
 }
 
-// Grid-wide barrier of the back-tracking workgroups (one per scheduled
-// maneuver): thread 0 counts its workgroup in (a release, after its
-// exchange writes) and polls, a bounded number of times, until `target`
-// workgroups have arrived.  False when it gave up.
-constexpr uint32_t kMaxPolls = 1u << 24;
-__device__ bool group_barrier(uint32_t* counter, uint32_t target, uint32_t* flag) {
-  if (threadIdx.x == 0) {
-    uint32_t ok = 1, polls = 0;
-    __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    while (__hip_atomic_load(counter, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (++polls > kMaxPolls) {
-        ok = 0;
-        break;
-      }
-      if (polls < 4096)
-        __builtin_amdgcn_s_sleep(1);
-      else
-        __builtin_amdgcn_s_sleep(32);
-    }
-    *flag = ok;
-  }
-  __syncthreads();
-  const bool ok = *flag != 0;
-  __syncthreads();
-  return ok;
-}
+// The workgroups of one plan's back-tracking (one per scheduled maneuver)
+// exchange their best candidates through two 64-bit words each, double-buffered
+// by step parity: word 0 holds the key and word 1 the candidate's pose and
+// value, each with two tag bits that differ between successive writes of a slot
+// (and from the zero it starts with).  A word is written and read whole, so a
+// reader that sees the step's tag has the step's data and no order between
+// words, no counter and no cache maintenance is needed: the tables and volumes,
+// which nothing writes meanwhile, stay cached from step to step.  A workgroup
+// is at most one step ahead of another, whose words of the step before are in
+// the other buffer.  Polls are bounded.
+constexpr uint32_t kMaxPolls = 1u << 22;
+constexpr int kExchangeWords = 2 * 6 * 2;  // 64-bit words: parities, slots, words
+static_assert(2 * kExchangeWords == kExSyncWords, "the extract area's words after the steps");
+__device__ __forceinline__ uint64_t step_tag(uint32_t iter) { return (uint64_t)(1u + (iter >> 1) % 3u) << 62; }
 
-__device__ __forceinline__ uint32_t load_shared_word(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// GROUP: workgroup g examines the candidates of schedule position g only and
-// the workgroups exchange their best (key, value, step cost) through the
-// words after the step list; every workgroup then takes the same decision.
-// Workgroup 0 writes the result.
-template <bool GROUP, int NT = kThreads>
-__device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[NT / 64], uint64_t* red64,
-                                             uint32_t* flag) {
+// Goal search: the best pose of the goal set or window, false if there is
+// none.  The first thread of the `writer` workgroup writes the result header.
+template <int NT>
+__device__ __forceinline__ bool goal_search(const ExArgs& x, uint64_t* red64, bool writer, int& ci, int& cj, int& cT) {
   constexpr int NW = NT / 64;
   const DevPlan& d = x.d;
   const int N = d.nx, L = d.nt;
   const int tid = threadIdx.x;
   uint32_t* out = d.extract;
-  const bool writer = !GROUP || blockIdx.x == 0;
-  uint32_t* sync = out + kExHeader + (size_t)NHP_MAX_STEPS_DEVICE * kExStepWords;
-
-  int ci, cj, cT;
   if (x.n_goals > 0) {
     // ---- goal set: smallest V + penalty, ties to the earlier goal ----
     uint64_t key = ~0ull;
@@ -285,7 +251,7 @@ __device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[
         out[0] = (uint32_t)(-NHP_EUNREACH);
         out[1] = 0;
       }
-      return;
+      return false;
     }
     const uint32_t* g = d.goals + 4 * (size_t)(key & 4095);
     ci = (int)g[0];
@@ -322,7 +288,7 @@ __device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[
         out[0] = (uint32_t)(-NHP_EUNREACH);
         out[1] = 0;
       }
-      return;
+      return false;
     }
     ci = modn((int)x.gi + (int)(key & 63) - r, N);
     cj = modn((int)x.gj + (int)((key >> 6) & 63) - r, N);
@@ -337,7 +303,66 @@ __device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[
     }
   }
 
-  // ---- back-tracking ----
+  return true;
+}
+
+// Seed slot that ends the plan at the current pose, or -1: the first seed
+// (start order, then along a maneuver in progress) at this pose whose value is
+// the current value.
+template <int NT>
+__device__ __forceinline__ int seed_at(const ExArgs& x, uint64_t* red64, uint32_t cur, uint32_t vcur) {
+  uint64_t hit = ~0ull;
+  const int slots = x.n_starts * x.d.seed_slots;
+  for (int e = threadIdx.x; e < slots; e += NT) {
+    const uint32_t* sd = x.d.seeds + (size_t)e * kSeedWords;
+    if (sd[0] == cur && sd[1] == vcur) hit = hit < (uint64_t)e ? hit : (uint64_t)e;
+  }
+  hit = block_min_u64<NT / 64>(hit, red64);
+  return hit != ~0ull ? (int)hit : -1;
+}
+
+__device__ __forceinline__ void write_step(uint32_t* out, uint32_t n, int mu, int k, int pi, int pj, int pT, int ci,
+                                           int cj, int cT, uint32_t cost) {
+  if (n >= NHP_MAX_STEPS_DEVICE) return;
+  uint32_t* s = out + kExHeader + (size_t)n * kExStepWords;
+  s[0] = mu;
+  s[1] = k;
+  s[2] = pi;
+  s[3] = pj;
+  s[4] = pT;
+  s[5] = ci;
+  s[6] = cj;
+  s[7] = cT;
+  s[8] = cost;
+}
+
+// End of a plan at pose (ci, cj, cT): a seed inside a maneuver in progress makes
+// that maneuver the first step; then status and step count.
+__device__ __forceinline__ void finish_plan(const ExArgs& x, int seed_hit, uint32_t status, uint32_t n, int ci, int cj,
+                                            int cT) {
+  uint32_t* out = x.d.extract;
+  if (seed_hit >= 0 && status == 0) {
+    const uint32_t* sd = x.d.seeds + (size_t)seed_hit * kSeedWords;
+    const nhp_start st = x.d.starts[sd[2]];
+    if (sd[3] > 0) {
+      write_step(out, n, st.maneuver, (int)sd[3], (int)st.i, (int)st.j, (int)st.T, ci, cj, cT, sd[1] - st.cost_q10);
+      n++;
+    }
+  }
+  out[0] = status;
+  out[1] = n;
+}
+
+// One workgroup per plan: every thread examines its candidate of each
+// scheduled maneuver.
+template <int NT>
+__device__ __forceinline__ void extract_alone(const ExArgs& x, uint32_t (*red32)[NT / 64], uint64_t* red64) {
+  constexpr int NW = NT / 64;
+  const DevPlan& d = x.d;
+  const int N = d.nx, L = d.nt;
+  const int tid = threadIdx.x;
+  int ci, cj, cT;
+  if (!goal_search<NT>(x, red64, true, ci, cj, cT)) return;
   uint32_t n = 0, status = 0;
   const int k = tid + 1;
   int seed_hit = -1;  // seed slot the plan ends at (start sets)
@@ -347,20 +372,8 @@ __device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[
   uint32_t vcur = d.V[pose_index(N, ci, cj, cT)];
   for (uint32_t iter = 0;; iter++) {
     if (x.n_starts > 0) {
-      // the first seed (start order, then along a maneuver in progress) at
-      // this pose whose value is the current value ends the plan
-      const uint32_t cur = (uint32_t)pose_index(N, ci, cj, cT);
-      uint64_t hit = ~0ull;
-      const int slots = x.n_starts * d.seed_slots;
-      for (int e = tid; e < slots; e += NT) {
-        const uint32_t* sd = d.seeds + (size_t)e * kSeedWords;
-        if (sd[0] == cur && sd[1] == vcur) hit = hit < (uint64_t)e ? hit : (uint64_t)e;
-      }
-      hit = block_min_u64<NW>(hit, red64);
-      if (hit != ~0ull) {
-        seed_hit = (int)hit;
-        break;
-      }
+      seed_hit = seed_at<NT>(x, red64, (uint32_t)pose_index(N, ci, cj, cT), vcur);
+      if (seed_hit >= 0) break;
     } else if ((uint32_t)ci == x.si && (uint32_t)cj == x.sj && (uint32_t)cT == x.st) {
       break;
     }
@@ -371,19 +384,17 @@ __device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[
       status = (uint32_t)(-NHP_EUNREACH);
       break;
     }
-    // candidates k = tid + 1 of every scheduled maneuver (GROUP: of this
-    // workgroup's one): all loads first
-    constexpr int M = GROUP ? 1 : 6;
+    // candidates k = tid + 1 of every scheduled maneuver: all loads first
+    constexpr int M = 6;
     uint32_t w[M], vq[M];
     bool ok[M];
 #pragma unroll
     for (int m = 0; m < M; m++) {
-      const int pos = GROUP ? (int)blockIdx.x : m;
       w[m] = kInf;
       vq[m] = kInf;
       ok[m] = false;
-      if (pos < d.n_schedule) {
-        const int mu = d.schedule[pos];
+      if (m < d.n_schedule) {
+        const int mu = d.schedule[m];
         int pi = 0, pj = 0, pT = 0;
         ok[m] = predecessor(d, mu, ci, cj, cT, k, &pi, &pj, &pT);
         if (ok[m]) {
@@ -397,11 +408,10 @@ __device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[
     uint64_t best = ~0ull;
 #pragma unroll
     for (int m = 0; m < M; m++) {
-      const int pos = GROUP ? (int)blockIdx.x : m;
-      if (pos < d.n_schedule) {
-        const uint32_t cand = sadd(sadd(vq[m], d.ct[d.schedule[pos]]), w[m]);
+      if (m < d.n_schedule) {
+        const uint32_t cand = sadd(sadd(vq[m], d.ct[d.schedule[m]]), w[m]);
         if (ok[m] && cand != kInf) {
-          const uint64_t k2 = ((uint64_t)cand << 14) | ((uint64_t)pos << 11) | (uint64_t)k;
+          const uint64_t k2 = ((uint64_t)cand << 14) | ((uint64_t)m << 11) | (uint64_t)k;
           best = k2 < best ? k2 : best;
         }
       }
@@ -413,55 +423,15 @@ __device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[
       const int bpos = (int)((best >> 11) & 7);
 #pragma unroll
       for (int m = 0; m < M; m++) {
-        if ((GROUP ? (int)blockIdx.x : m) == bpos) {
+        if (m == bpos) {
           red32[0][0] = vq[m];
           red32[0][1] = sadd(d.ct[d.schedule[bpos]], w[m]);
         }
       }
     }
     __syncthreads();
-    uint32_t vnext = red32[0][0], cost = red32[0][1];
+    const uint32_t vnext = red32[0][0], cost = red32[0][1];
     __syncthreads();  // red32 is reused by the next step's scan
-    if (GROUP) {
-      // exchange the workgroups' bests (double-buffered by step parity, so a
-      // fast workgroup's next writes never meet a slow one's reads)
-      uint32_t* mine = sync + 1 + ((iter & 1) * 6 + blockIdx.x) * 4;
-      if (tid == 0) {
-        mine[0] = (uint32_t)best;
-        mine[1] = (uint32_t)(best >> 32);
-        mine[2] = vnext;
-        mine[3] = cost;
-      }
-      if (!group_barrier(sync, gridDim.x * (iter + 1), flag)) {
-        status = (uint32_t)(-NHP_EHIP);
-        break;
-      }
-      // the four words of all 6 slots read in one round (the area always
-      // holds 6; slots past the grid are read and ignored), then the best
-      // of the grid's workgroups taken
-      uint32_t ex[6][4];
-      const uint32_t* slots = sync + 1 + (iter & 1) * 6 * 4;
-#pragma unroll
-      for (int g = 0; g < 6; g++) {
-#pragma unroll
-        for (int m = 0; m < 4; m++) ex[g][m] = load_shared_word(slots + g * 4 + m);
-      }
-#pragma unroll
-      for (int g = 0; g < 6; g++)
-        asm volatile("" : "+v"(ex[g][0]), "+v"(ex[g][1]), "+v"(ex[g][2]), "+v"(ex[g][3]));  // all arrived first
-      best = ~0ull;
-#pragma unroll
-      for (int g = 0; g < 6; g++) {
-        if (g < (int)gridDim.x) {
-          const uint64_t kg = (uint64_t)ex[g][0] | ((uint64_t)ex[g][1] << 32);
-          if (kg < best) {
-            best = kg;
-            vnext = ex[g][2];
-            cost = ex[g][3];
-          }
-        }
-      }
-    }
     if (best == ~0ull) {
       status = (uint32_t)(-NHP_EUNREACH);
       break;
@@ -470,69 +440,206 @@ __device__ __forceinline__ void extract_body(const ExArgs& x, uint32_t (*red32)[
     const int mu = d.schedule[pos];
     int pi, pj, pT;
     predecessor(d, mu, ci, cj, cT, kb, &pi, &pj, &pT);
-    if (tid == 0 && writer && n < NHP_MAX_STEPS_DEVICE) {
-      uint32_t* s = out + kExHeader + (size_t)n * kExStepWords;
-      s[0] = mu;
-      s[1] = kb;
-      s[2] = pi;
-      s[3] = pj;
-      s[4] = pT;
-      s[5] = ci;
-      s[6] = cj;
-      s[7] = cT;
-      s[8] = cost;
-    }
+    if (tid == 0) write_step(d.extract, n, mu, kb, pi, pj, pT, ci, cj, cT, cost);
     n++;
     ci = pi;
     cj = pj;
     cT = pT;
     vcur = vnext;
   }
-  if (seed_hit >= 0 && status == 0) {
-    // a seed inside a maneuver in progress: that maneuver is the first step
-    const uint32_t* sd = d.seeds + (size_t)seed_hit * kSeedWords;
-    const nhp_start st = d.starts[sd[2]];
-    if (sd[3] > 0) {
-      if (tid == 0 && writer && n < NHP_MAX_STEPS_DEVICE) {
-        uint32_t* o = out + kExHeader + (size_t)n * kExStepWords;
-        o[0] = (uint32_t)st.maneuver;
-        o[1] = sd[3];
-        o[2] = st.i;
-        o[3] = st.j;
-        o[4] = st.T;
-        o[5] = ci;
-        o[6] = cj;
-        o[7] = cT;
-        o[8] = sd[1] - st.cost_q10;
-      }
-      n++;
+  if (tid == 0) finish_plan(x, seed_hit, status, n, ci, cj, cT);
+}
+
+// The tables of one maneuver's curves in LDS, read once per plan: a step then
+// waits for one round of global loads, its candidates' codes and values.
+struct CurveTables {
+  uint32_t off[1024];    // turns: ox | oy << 16 by plane; straights: edge length
+  double slope[1024];    // straights: slope of the plane's lines (HostTables::slope)
+  uint8_t flags[1024];   // straights: 1 x-major, 2 the walk ascends
+};
+
+__device__ __forceinline__ void load_tables(const DevPlan& d, int mu, CurveTables& t) {
+  const int L = d.nt;
+  if (mu != NHP_SF && mu != NHP_SB) {
+    const int32_t* ox = d.turn_off + ((mu == NHP_LF || mu == NHP_LB) ? 0 : 2) * L;
+    for (int T = threadIdx.x; T < L; T += blockDim.x) t.off[T] = (uint32_t)ox[T] | ((uint32_t)ox[L + T] << 16);
+  } else {
+    for (int T = threadIdx.x; T < L; T += blockDim.x) {
+      t.off[T] = d.edge_len[(size_t)mu * L + T];
+      t.slope[T] = d.slope[T];
+      t.flags[T] = (uint8_t)((d.family[T] == 0 ? 1 : 0) | ((d.fwd[T] > 0) == (mu == NHP_SF) ? 2 : 0));
     }
-  }
-  if (tid == 0 && writer) {
-    out[0] = status;
-    out[1] = n;
   }
 }
 
-// one workgroup per scheduled maneuver (see extract_body), NT threads: at
+// The skew B(y, T) of eq. (22) as the host tables hold it: y times the plane's
+// slope, rounded half away from zero.
+__device__ __forceinline__ int skew_at(double slope, int y) {
+#pragma clang fp contract(off)
+  const double v = (double)y * slope, a = fabs(v);
+  const int i = (int)a, r = i + ((a - (double)i) >= 0.5 ? 1 : 0);
+  return v < 0 ? -r : r;
+}
+
+// `predecessor` from the tables in LDS.
+__device__ __forceinline__ bool table_predecessor(const DevPlan& d, const CurveTables& t, int mu, int i, int j, int T,
+                                                  int k, int& pi, int& pj, int& pT) {
+  const int N = d.nx, L = d.nt;
+  if (mu != NHP_SF && mu != NHP_SB) {
+    if (k >= L) return false;
+    const bool asc = (mu == NHP_LF || mu == NHP_RB);
+    const int Tk = wrapn(asc ? T - k : T + k, L);
+    const uint32_t o = t.off[T], ok = t.off[Tk];
+    const int xp = wrapn(i - (int)(o & 0xffffu), N), yp = wrapn(j - (int)(o >> 16), N);
+    pi = wrapn(xp + (int)(ok & 0xffffu), N);
+    pj = wrapn(yp + (int)(ok >> 16), N);
+    pT = Tk;
+    return true;
+  }
+  const bool fam_x = (t.flags[T] & 1) != 0, asc = (t.flags[T] & 2) != 0;
+  const double slope = t.slope[T];
+  const int c = fam_x ? i : j, other = fam_x ? j : i;
+  const int step = asc ? c : N - 1 - c;  // the kernels walk N-1 .. 0 when descending
+  if (k > step) return false;
+  const int xp = wrapn(other - skew_at(slope, c), N);
+  const int c2 = asc ? step - k : N - 1 - (step - k);
+  const int o2 = wrapn(xp + skew_at(slope, c2), N);
+  pi = fam_x ? c2 : o2;
+  pj = fam_x ? o2 : c2;
+  pT = T;
+  return true;
+}
+
+// One workgroup per scheduled maneuver: workgroup g examines the candidates of
+// schedule position g, the workgroups exchange their best, and every one takes
+// the same decision.  Workgroup 0 writes the result.  A step is a chain of
+// latencies: one round of loads, the block's scan and minimum, and the exchange
+// (512^3 maze, 61 steps: 291 us; with a counter barrier, its cache maintenance and
+// the tables read from memory in every step 420 us).
+template <int NT>
+__device__ __forceinline__ void extract_group(const ExArgs& x, uint32_t (*red32)[NT / 64], uint64_t* red64,
+                                              CurveTables& tab, uint64_t* ex, uint32_t* sh) {
+  constexpr int NW = NT / 64;
+  const DevPlan& d = x.d;
+  const int N = d.nx;
+  const int tid = threadIdx.x, pos = blockIdx.x, groups = gridDim.x;
+  const bool writer = pos == 0;
+  uint64_t* words = reinterpret_cast<uint64_t*>(x.exchange);
+  if (x.exchange_next && pos == 0 && tid < kExchangeWords) reinterpret_cast<uint64_t*>(x.exchange_next)[tid] = 0;
+  const int mu = d.schedule[pos];
+  const uint32_t ct = d.ct[mu];
+  load_tables(d, mu, tab);
+  int ci, cj, cT;
+  if (!goal_search<NT>(x, red64, writer, ci, cj, cT)) return;  // (the same in every workgroup)
+  uint32_t n = 0, status = 0;
+  const int k = tid + 1;
+  int seed_hit = -1;
+  uint32_t vcur = d.V[pose_index(N, ci, cj, cT)];
+  const bool turn = mu != NHP_SF && mu != NHP_SB;
+  __syncthreads();  // tables
+  for (uint32_t iter = 0;; iter++) {
+    if (x.n_starts > 0) {
+      seed_hit = seed_at<NT>(x, red64, (uint32_t)pose_index(N, ci, cj, cT), vcur);
+      if (seed_hit >= 0) break;
+    } else if ((uint32_t)ci == x.si && (uint32_t)cj == x.sj && (uint32_t)cT == x.st) {
+      break;
+    }
+    if (iter > NHP_MAX_STEPS_DEVICE || vcur == kInf) {  // (see extract_alone)
+      status = (uint32_t)(-NHP_EUNREACH);
+      break;
+    }
+    uint32_t w[1] = {kInf}, vq = kInf;
+    int pi = 0, pj = 0, pT = 0;
+    const bool ok = table_predecessor(d, tab, mu, ci, cj, cT, k, pi, pj, pT);
+    if (ok) {
+      const size_t q = pose_index(N, pi, pj, pT);
+      w[0] = weight(d.B[q], turn ? d.turn_lq[mu] : tab.off[pT]);
+      vq = d.V[q];
+    }
+    block_scan_sat<1, NW>(w, red32);  // becomes the edge sum E_k
+    uint64_t best = ~0ull;
+    const uint32_t cand = sadd(sadd(vq, ct), w[0]);
+    if (ok && cand != kInf) best = ((uint64_t)cand << 14) | ((uint64_t)pos << 11) | (uint64_t)k;
+    best = block_min_u64<NW>(best, red64);
+    // publish: the thread that holds the best candidate, or any if there is none
+    uint64_t* slot = words + ((iter & 1u) * 6u + (uint32_t)pos) * 2u;
+    if (best != ~0ull ? k == (int)(best & 2047) : tid == 0) {
+      const uint64_t key = best != ~0ull ? best : (1ull << 62) - 1ull;
+      const uint64_t pose = ((uint64_t)pT << 20) | ((uint64_t)pj << 10) | (uint64_t)pi;
+      __hip_atomic_store(slot, step_tag(iter) | key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(slot + 1, step_tag(iter) | (pose << 32) | vq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (tid < 64) {
+      // lanes 0..11 wait for the slots' words
+      uint64_t v = step_tag(iter);
+      if (tid < 2 * groups) {
+        const uint64_t* p = words + (iter & 1u) * 12u + (uint32_t)tid;
+        uint32_t polls = 0;
+        do {
+          v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } while ((v & (3ull << 62)) != step_tag(iter) && ++polls < kMaxPolls);
+      }
+      if (tid < 12) ex[tid] = v & ((1ull << 62) - 1ull);
+      const bool all = __builtin_amdgcn_ballot_w64((v & (3ull << 62)) != step_tag(iter)) == 0ull;
+      if (tid == 0) *sh = all ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!*sh) {
+      status = (uint32_t)(-NHP_EHIP);
+      break;
+    }
+    uint64_t key = (1ull << 62) - 1ull, rest = 0;
+    for (int g = 0; g < groups; g++) {
+      const uint64_t kg = ex[2 * g];
+      if (kg < key) {
+        key = kg;
+        rest = ex[2 * g + 1];
+      }
+    }
+    __syncthreads();  // ex is rewritten by the next step
+    if (key == (1ull << 62) - 1ull) {
+      status = (uint32_t)(-NHP_EUNREACH);
+      break;
+    }
+    const uint32_t vnext = (uint32_t)rest, pose = (uint32_t)(rest >> 32);
+    pi = (int)(pose & 1023u);
+    pj = (int)((pose >> 10) & 1023u);
+    pT = (int)((pose >> 20) & 1023u);
+    // the step costs what the candidate is above its pose's value (nothing saturated)
+    if (tid == 0 && writer)
+      write_step(d.extract, n, d.schedule[(key >> 11) & 7], (int)(key & 2047), pi, pj, pT, ci, cj, cT,
+                 (uint32_t)(key >> 14) - vnext);
+    n++;
+    ci = pi;
+    cj = pj;
+    cT = pT;
+    vcur = vnext;
+  }
+  if (tid == 0 && writer) finish_plan(x, seed_hit, status, n, ci, cj, cT);
+}
+
+// one workgroup per scheduled maneuver (see extract_group), NT threads: at
 // least one per candidate, i.e. more than the longest curve (max(nx, ntheta) - 1
 // poses), in as few waves as that allows
 template <int NT>
 __global__ __launch_bounds__(NT) void extract_kernel(ExArgs x) {
-  __shared__ uint32_t red32[6][NT / 64];
-  __shared__ uint64_t red64[NT / 64];
+  __shared__ uint32_t red32[1][NT / 64];
+  __shared__ uint64_t red64[NT / 64], ex[12];
   __shared__ uint32_t flag;
-  extract_body<true, NT>(x, red32, red64, &flag);
+  __shared__ CurveTables tab;
+  extract_group<NT>(x, red32, red64, tab, ex, &flag);
 }
 
-__global__ void clear_word_kernel(uint32_t* w) { *w = 0; }
+__global__ void clear_exchange_kernel(uint32_t* w) {
+  if (threadIdx.x < 2 * kExchangeWords) w[threadIdx.x] = 0;
+}
 
 // one workgroup per plan
 __global__ __launch_bounds__(kThreads) void extract_batch_kernel(const ExArgs* __restrict__ args) {
   __shared__ uint32_t red32[6][kWaves];
   __shared__ uint64_t red64[kWaves];
   const ExArgs x = args[blockIdx.x];
-  extract_body<false>(x, red32, red64, nullptr);
+  extract_alone<kThreads>(x, red32, red64);
 }
 
 // ---- reachability (App. C): goal search and back-tracking on level bits ----
@@ -664,14 +771,14 @@ hipError_t launch_reach_extract(const ReachExArgs& x, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_extract(const ExArgs& x, hipStream_t s) {
+hipError_t launch_extract(const ExArgs& x, bool clear, hipStream_t s) {
   if (x.d.n_schedule < 1 || x.d.n_schedule > 6) return hipErrorInvalidValue;
-  // the barrier counter starts at zero (a kernel, not a memset node, so the
-  // call may be captured)
-  hipLaunchKernelGGL(clear_word_kernel, dim3(1), dim3(1), 0, s,
-                     x.d.extract + kExHeader + (size_t)NHP_MAX_STEPS_DEVICE * kExStepWords);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (clear) {
+    // (a kernel, not a memset node, so the call may be captured)
+    hipLaunchKernelGGL(clear_exchange_kernel, dim3(1), dim3(64), 0, s, x.exchange);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   const int len = x.d.nx > x.d.nt ? x.d.nx : x.d.nt;
   if (len <= 256)
     hipLaunchKernelGGL(extract_kernel<256>, dim3(x.d.n_schedule), dim3(256), 0, s, x);
@@ -688,7 +795,7 @@ hipError_t launch_seed(const DevPlan& d, int n_starts, hipStream_t s) {
 }
 
 // ---- extract area of extract_path_noalloc ----
-// One extract area (header, step list, barrier counter and exchange area) per
+// One extract area (header, step list and exchange words) per
 // device, in a file-scope device array instead of a plan's workspace, for
 // callers that cannot allocate.  Every call on a device shares its copy.
 static __device__ __align__(256) uint32_t scratch[kNoAllocExtractWords];

@@ -57,7 +57,7 @@ int hip_fail(hipError_t e, const char* what) {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
-  size_t V, B, turn_off, skew, edge_len, fwd, family, planes, slot, stamps, taps, extract, starts, seeds, goals, total;
+  size_t V, B, turn_off, skew, slope, edge_len, fwd, family, planes, slot, stamps, taps, extract, starts, seeds, goals, total;
 };
 
 static_assert(NHP_MAX_GOALS * 16 >= NHP_MAX_SOFT_TABLE, "the soft-cost table lives in the goal-set buffer");
@@ -92,6 +92,8 @@ Layout layout_of(const nhp_params& p) {
   o = align256(o + 4 * (size_t)p.ntheta * 4);
   l.skew = o;
   o = align256(o + (size_t)p.ntheta * p.nx * 2);
+  l.slope = o;
+  o = align256(o + (size_t)p.ntheta * 8);
   l.edge_len = o;
   o = align256(o + 6 * (size_t)p.ntheta * 4);
   l.fwd = o;
@@ -107,7 +109,7 @@ Layout layout_of(const nhp_params& p) {
   l.taps = o;
   o = align256(o + (size_t)p.ntheta * 2 * nhp::kMaxTaps * 4);
   l.extract = o;
-  o = align256(o + (nhp::kExHeader + (size_t)NHP_MAX_STEPS_DEVICE * nhp::kExStepWords + nhp::kExSyncWords) * 4);
+  o = align256(o + nhp::kExPlanWords * 4);
   l.starts = o;
   o = align256(o + NHP_MAX_STARTS * sizeof(nhp_start));
   l.seeds = o;
@@ -184,6 +186,19 @@ int nhp::track_plan(nhp_plan* plan, hipStream_t stream) {
   return NHP_OK;
 }
 
+// The plan's two areas of exchange words take turns: an extraction clears the
+// one that the next takes, so a clearing launch is needed only before the first
+// and after one that did not run to its end (finish_extract sets ex_clear).
+static hipError_t launch_plan_extract(nhp_plan* plan, nhp::ExArgs& x) {
+  uint32_t* words = plan->d.extract + nhp::kExAreaWords;
+  x.exchange = words + plan->ex_turn * nhp::kExSyncWords;
+  plan->ex_turn ^= 1u;
+  x.exchange_next = words + plan->ex_turn * nhp::kExSyncWords;
+  const bool clear = !plan->ex_clear;
+  plan->ex_clear = false;
+  return nhp::launch_extract(x, clear, plan->stream);
+}
+
 static int finish_extract(nhp_plan* plan, nhp_step* h_steps, uint32_t cap, uint32_t* n_steps, uint32_t* best_ijt,
                           uint32_t* best_index, uint32_t* goal_value_q10, uint32_t* score_q10);
 
@@ -255,6 +270,7 @@ int plan_create(const nhp_params* params, void* d_workspace, size_t workspace_by
   d.B = reinterpret_cast<uint8_t*>(base + l.B);
   d.turn_off = reinterpret_cast<int32_t*>(base + l.turn_off);
   d.skew = reinterpret_cast<int16_t*>(base + l.skew);
+  d.slope = reinterpret_cast<double*>(base + l.slope);
   d.edge_len = reinterpret_cast<uint32_t*>(base + l.edge_len);
   d.fwd = reinterpret_cast<int32_t*>(base + l.fwd);
   d.family = reinterpret_cast<int32_t*>(base + l.family);
@@ -287,6 +303,7 @@ int plan_create(const nhp_params* params, void* d_workspace, size_t workspace_by
     size_t n;
   } ups[] = {
       {d.turn_off, t.turn_off.data(), t.turn_off.size() * 4}, {d.skew, t.skew16->data(), t.skew16->size() * 2},
+      {d.slope, t.slope.data(), t.slope.size() * 8},
       {d.edge_len, t.edge_len.data(), t.edge_len.size() * 4}, {d.fwd, t.fwd.data(), t.fwd.size() * 4},
       {d.family, t.family.data(), t.family.size() * 4},       {d.planes, planes.data(), planes.size() * 4},
       {d.slot, plan->slot.data(), plan->slot.size() * 4},
@@ -618,7 +635,7 @@ int extract_path(nhp_plan* plan, uint32_t gi, uint32_t gj, uint32_t gt, uint32_t
   x.w_xy = w_xy_q10;
   x.w_t = w_t_q10;
   x.n_starts = plan->n_starts;
-  HIP_CHECK(nhp::launch_extract(x, plan->stream), "extract launch");
+  HIP_CHECK(launch_plan_extract(plan, x), "extract launch");
   return finish_extract(plan, h_steps, cap, n_steps, best_ijt, nullptr, goal_value_q10, score_q10);
 }
 
@@ -652,7 +669,8 @@ int extract_path_noalloc(nhp_plan* plan, uint32_t gi, uint32_t gj, uint32_t gt, 
   x.w_xy = w_xy_q10;
   x.w_t = w_t_q10;
   x.n_starts = plan->n_starts;
-  HIP_CHECK(nhp::launch_extract(x, plan->stream), "extract launch");
+  x.exchange = area + nhp::kExAreaWords;
+  HIP_CHECK(nhp::launch_extract(x, true, plan->stream), "extract launch");
   uint32_t head[nhp::kExHeader];
   HIP_CHECK(hipMemcpyAsync(head, area, sizeof(head), hipMemcpyDeviceToHost, plan->stream), "extract copy");
   HIP_CHECK(hipStreamSynchronize(plan->stream), "extract copy");
@@ -709,6 +727,7 @@ static int finish_extract(nhp_plan* plan, nhp_step* h_steps, uint32_t cap, uint3
   if (n_steps) *n_steps = n;
   if (status != 0 && status != (uint32_t)(-NHP_EUNREACH))
     return fail(NHP_EHIP, "extract kernel returned status %u", status);
+  plan->ex_clear = true;
   if (status == (uint32_t)(-NHP_EUNREACH))
     return fail(NHP_EUNREACH, "no reached pose in the goal window (or back-tracking lost the path)");
   if (best_ijt) memcpy(best_ijt, head + 2, 3 * sizeof(uint32_t));
@@ -769,7 +788,7 @@ int extract_path_set(nhp_plan* plan, const uint32_t* goals_ijt, const uint32_t* 
   x.st = plan->start[2];
   x.n_goals = (int)n_goals;
   x.n_starts = plan->n_starts;
-  HIP_CHECK(nhp::launch_extract(x, plan->stream), "extract launch");
+  HIP_CHECK(launch_plan_extract(plan, x), "extract launch");
   // finish_extract synchronises, so the pageable goal copy has completed
   return finish_extract(plan, h_steps, cap, n_steps, nullptr, best_index, goal_value_q10, score_q10);
 }

@@ -603,7 +603,7 @@ int batch_extract(nhp_batch* b, nhp_plan* const* plans, uint32_t n, const uint32
       return nhp::set_error(NHP_EINVAL, "goal of plans[%u] outside its grid", k);
     if (radius[k] > (uint32_t)nhp::kMaxRadius) return nhp::set_error(NHP_EINVAL, "goal radius of plans[%u] > 31", k);
     args[k] = nhp::ExArgs{p->d, p->start[0], p->start[1], p->start[2], gi, gj, gt, (int)radius[k], w_xy_q10[k],
-                          w_t_q10[k], 0, p->n_starts};
+                          w_t_q10[k], 0, p->n_starts, nullptr, nullptr};
   }
   // each plan's header and first kReadbackSteps steps come back in one copy
   // to the pinned slot; only longer paths need a second copy

@@ -28,6 +28,7 @@ struct HostTables {
   // and is shared by every plan of that shape in the process
   std::shared_ptr<const std::vector<int16_t>> skew16;
   // derived device layouts
+  std::vector<double> slope;      // [T] slope K of eq. (20) of the plane's own family
   std::vector<int32_t> turn_off;  // [4][T]: LEFT x, LEFT y, RIGHT x, RIGHT y, reduced mod nx
   std::vector<int32_t> planes_x;  // heading planes of the x-major straight family (I = 0)
   std::vector<int32_t> planes_y;  // heading planes of the y-major straight family (I = 1)
@@ -46,6 +47,7 @@ struct DevPlan {
   uint8_t* B;            // obstacle volume, N_R codes
   int32_t* turn_off;     // [4][nt]
   int16_t* skew;         // [nt][nx]
+  double* slope;         // [nt]
   uint32_t* edge_len;    // [6][nt]
   int32_t* fwd;          // [nt]
   int32_t* family;       // [nt]
@@ -217,9 +219,13 @@ hipError_t launch_init_batch(const InitJob* d_jobs, int n_jobs, size_t max_n4, h
 constexpr int kExHeader = 16;  // status, n_steps, best i, j, T, V(best), score, best goal index, ...
 constexpr int kExStepWords = 9;
 constexpr int kReadbackSteps = 256;  // steps read back with the header in one copy
-// after the steps: a barrier counter and, per step parity and schedule
-// position, the best candidate key (2 words), its pose's value and the cost
-constexpr int kExSyncWords = 1 + 2 * 6 * 4;
+// after the steps: per step parity and schedule position, the best candidate's
+// key, and its pose and value (two 64-bit words).  A plan has two such areas,
+// which its launches take in turns (kExPlanWords words in all).
+constexpr int kExSyncWords = 2 * 6 * 4;
+constexpr size_t kExAreaWords = kExHeader + (size_t)NHP_MAX_STEPS_DEVICE * kExStepWords;  // words before them
+constexpr size_t kExPlanWords = kExAreaWords + 2 * kExSyncWords;
+static_assert(kExAreaWords % 2 == 0 && kExSyncWords % 2 == 0, "64-bit words");
 // seed entry: pose index (kNoSeed when unused), value, start index, edges along its maneuver
 constexpr int kSeedWords = 4;
 constexpr uint32_t kNoSeed = 0xFFFFFFFFu;
@@ -242,7 +248,8 @@ hipError_t launch_sweep(const DevPlan& d, Pass pass, hipStream_t s, TrackState* 
 // straight planes), bit 1 = the x-major straight planes.
 hipError_t launch_sweep_part(const DevPlan& d, Pass pass, int parts, hipStream_t s, TrackState* ts = nullptr);
 hipError_t launch_render(const DevPlan& d, const uint8_t* image, int n_side, int n_len, hipStream_t s);
-hipError_t launch_extract(const struct ExArgs& x, hipStream_t s);
+// clear: x.exchange may hold anything (it is cleared first).
+hipError_t launch_extract(const struct ExArgs& x, bool clear, hipStream_t s);
 
 // Goal search and back-tracking arguments of one plan.
 struct ExArgs {
@@ -252,10 +259,13 @@ struct ExArgs {
   uint32_t w_xy, w_t;
   int n_goals;   // > 0: goal set in d.goals instead of the window
   int n_starts;  // > 0: the plan ends at a seed of the start set in d.seeds
+  // one plan's workgroups: exchange words, all zero, and the words the next
+  // launch will take, which this one clears (nullptr: none)
+  uint32_t *exchange, *exchange_next;
 };
 hipError_t launch_extract_batch(const ExArgs* d_args, int n, hipStream_t s);
-// Words of one extract area (header, steps, barrier counter, exchange area).
-constexpr size_t kNoAllocExtractWords = kExHeader + (size_t)NHP_MAX_STEPS_DEVICE * kExStepWords + kExSyncWords;
+// Words of one extract area (header, steps, exchange words).
+constexpr size_t kNoAllocExtractWords = kExAreaWords + kExSyncWords + 1;  // (the last is spare)
 static_assert(kNoAllocExtractWords * 4 == NHP_NOALLOC_EXTRACT_BYTES, "the header states the area's size");
 // Device address of the file-scope extract area on `device` (looked up on
 // the first call per device; no allocation).
@@ -356,6 +366,8 @@ struct nhp_plan {
   int n_starts = 0;  // > 0: the value volume was seeded from a start set
   bool graph_failed = false;  // capture unavailable: launch the kernels directly
   uint32_t multi_cycle_runs = 0;  // sweeps of more than one cycle so far (graphs from the second on)
+  uint32_t ex_turn = 0;   // exchange words (0, 1) that the next extraction takes
+  bool ex_clear = false;  // ... and whether a finished one has cleared them
   uint32_t* readback = nullptr;  // pinned: extract header and the first kReadbackSteps steps
 };
 

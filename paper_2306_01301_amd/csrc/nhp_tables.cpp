@@ -69,6 +69,12 @@ double grid_cos(int nt, long T) { return grid_sin(nt, T + nt / 4); }
 
 namespace {
 
+// eq. (20): the slope of plane T's lines in its own family
+double plane_slope(int L, int T) {
+  const double s = grid_sin(L, T), c = grid_cos(L, T);
+  return x_major_plane(L, T) ? s / c : c / s;
+}
+
 // Skew table of eq. (22) for all planes of one shape: B(y', T) =
 // round(y' K_T) with K_T the plane's slope of eq. (20), in the plane's own
 // family.  A process-wide cache keyed by (nx, ntheta) builds each shape once
@@ -86,8 +92,7 @@ std::shared_ptr<const std::vector<int16_t>> skew_table(int N, int L) {
   }
   auto table = std::make_shared<std::vector<int16_t>>((size_t)L * N);
   for (int T = 0; T < L; T++) {
-    const double s = grid_sin(L, T), c = grid_cos(L, T);
-    const double K = x_major_plane(L, T) ? s / c : c / s;
+    const double K = plane_slope(L, T);
     int16_t* row = table->data() + (size_t)T * N;
     for (int y = 0; y < N; y++) row[y] = (int16_t)round_half_away((double)y * K);
   }
@@ -148,6 +153,8 @@ int build_tables(const nhp_params& p, HostTables& t) {
     t.turn_off[3 * L + T] = mod(t.beta[(T + 1 * q) % L], N);
   }
   t.skew16 = skew_table(N, L);
+  t.slope.resize(L);
+  for (int T = 0; T < L; T++) t.slope[T] = plane_slope(L, T);
   return NHP_OK;
 }
 

@@ -101,3 +101,39 @@ def test_straight_chunks_match_oracle(n, nt):
         oracle.sweep(prob, mu, B, V)
         assert np.array_equal(p.value_numpy(), V)
     p.close()
+
+
+# both sides of each thread count of the back-tracking workgroups, the longest
+# curves, one maneuver and all six: a plan's cooperating workgroups against the
+# batched kernel's one, over many goals in turn (reached, unreached, the start)
+@pytest.mark.parametrize("n,nt,schedule", [
+    (16, 8, scenes.DEFAULT_SCHEDULE), (200, 72, scenes.DEFAULT_SCHEDULE), (256, 256, scenes.DEFAULT_SCHEDULE),
+    (264, 40, scenes.DEFAULT_SCHEDULE), (64, 512, scenes.DEFAULT_SCHEDULE), (64, 520, scenes.DEFAULT_SCHEDULE),
+    (1024, 16, scenes.DEFAULT_SCHEDULE), (32, 1024, scenes.DEFAULT_SCHEDULE), (72, 64, scenes.FORWARD_SCHEDULE),
+    (72, 64, (P.SF,)), (72, 64, (P.RB,))])
+def test_extract_workgroups_agree(n, nt, schedule):
+    print("extract %d x %d" % (n, nt), flush=True)
+    rng = np.random.default_rng(n + nt)
+    sc = scenes.random_small(n, n=n, nt=nt, R=max(2.0, n / 16), n_rect=6).with_(
+        vehicle=(2, 1, 1), start=(n // 2, n // 3, nt // 5), schedule=tuple(schedule))
+    img = sc.image.copy()
+    img[n // 3 - 4:n // 3 + 5, n // 2 - 4:n // 2 + 5] = 0
+    pl, batch = P.planner_for(sc), P.Batch(1)
+    pl.render(_dev(img), sc.vehicle)
+    pl.sweep(sc.start, 3)
+    reached = np.argwhere(pl.value.cpu().numpy().view(np.uint32) != 0xFFFFFFFF)[:, ::-1]
+    assert len(reached) > 1
+    for r in range(24):
+        goal = rng.integers(0, (n, n, nt)) if r % 2 else reached[rng.integers(len(reached))]
+        goal = sc.start if r == 5 else tuple(int(v) for v in goal)
+        radius = int(rng.integers(0, 4))
+        want = batch.extract([pl], [goal], [radius], [1024], [700])[0]
+        for call in (pl.extract, pl.extract_noalloc):
+            try:
+                got = call(goal, radius, 1024, 700)
+            except P.NhpError as e:
+                got = e.rc
+            assert got == want
+        assert r % 2 or not isinstance(want, int)
+    batch.close()
+    pl.close()
