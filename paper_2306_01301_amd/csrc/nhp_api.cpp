@@ -297,28 +297,26 @@ int plan_create(const nhp_params* params, void* d_workspace, size_t workspace_by
   planes.insert(planes.end(), t.planes_y.begin(), t.planes_y.end());
   plan->slot.resize(planes.size());
   for (size_t k = 0; k < planes.size(); k++) plan->slot[planes[k]] = (int32_t)k;
+  // the tables lie side by side in the workspace: one copy for all of them
+  // (64^3 plan: creation 89 us with a copy per table, 38 us with one)
   struct Up {
-    void* dst;
+    size_t at;
     const void* src;
     size_t n;
   } ups[] = {
-      {d.turn_off, t.turn_off.data(), t.turn_off.size() * 4}, {d.skew, t.skew16->data(), t.skew16->size() * 2},
-      {d.slope, t.slope.data(), t.slope.size() * 8},
-      {d.edge_len, t.edge_len.data(), t.edge_len.size() * 4}, {d.fwd, t.fwd.data(), t.fwd.size() * 4},
-      {d.family, t.family.data(), t.family.size() * 4},       {d.planes, planes.data(), planes.size() * 4},
-      {d.slot, plan->slot.data(), plan->slot.size() * 4},
+      {l.turn_off, t.turn_off.data(), t.turn_off.size() * 4}, {l.skew, t.skew16->data(), t.skew16->size() * 2},
+      {l.slope, t.slope.data(), t.slope.size() * 8},          {l.edge_len, t.edge_len.data(), t.edge_len.size() * 4},
+      {l.fwd, t.fwd.data(), t.fwd.size() * 4},                {l.family, t.family.data(), t.family.size() * 4},
+      {l.planes, planes.data(), planes.size() * 4},           {l.slot, plan->slot.data(), plan->slot.size() * 4},
   };
-  for (const Up& u : ups) {
-    e = hipMemcpyAsync(u.dst, u.src, u.n, hipMemcpyHostToDevice, plan->stream);
-    if (e == hipSuccess) continue;
-    plan_destroy(plan);
-    return hip_fail(e, "table upload");
-  }
-  // the host vectors above are pageable and `planes` is local: wait for the copies
-  e = hipStreamSynchronize(plan->stream);
+  std::vector<char> image(l.stamps - l.turn_off);
+  for (const Up& u : ups) memcpy(image.data() + (u.at - l.turn_off), u.src, u.n);
+  e = hipMemcpyAsync(base + l.turn_off, image.data(), image.size(), hipMemcpyHostToDevice, plan->stream);
+  // `image` is pageable and local: wait for the copy
+  if (e == hipSuccess) e = hipStreamSynchronize(plan->stream);
   if (e != hipSuccess) {
     plan_destroy(plan);
-    return hip_fail(e, "hipStreamSynchronize");
+    return hip_fail(e, "table upload");
   }
   *out = plan;
   return ok();
