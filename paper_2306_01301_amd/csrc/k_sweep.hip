@@ -89,6 +89,7 @@ template <int Q, int NT, int BUFS, bool TRACK>
 __global__ __launch_bounds__(NT, (xband_waves_per_simd<Q, NT, BUFS>())) void xmajor_band_kernel(SweepJob job) {
   __shared__ XBand<Q, NT, BUFS> sh;
   for (int i = threadIdx.x; i < 2 * XBand<Q, NT, BUFS>::BROWS; i += NT) sh.dirty[i & 1][i >> 1] = 0;
+  if (threadIdx.x < 2) sh.any[threadIdx.x] = 0;
   uint32_t chunks = 0;  // (the tile's first barrier orders the clearing before any flag is set)
   for (int b = blockIdx.x; b < job.blocks; b += gridDim.x) {
     const int tile = tile_of(b, job.blocks, job.order);

@@ -96,6 +96,7 @@ __global__ __launch_bounds__(NT, (xband_waves_per_simd<Q, NT, BUFS>())) void xma
   const int j = __builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, t));
   const SweepJob job = jobs[j];
   for (int i = threadIdx.x; i < 2 * XBand<Q, NT, BUFS>::BROWS; i += NT) sh.dirty[i & 1][i >> 1] = 0;
+  if (threadIdx.x < 2) sh.any[threadIdx.x] = 0;
   uint32_t chunks = 0;
   xmajor_band_tile<Q, NT, BUFS, XBPREF, false>(job, t - job.first_block, sh, chunks);
 }
@@ -106,6 +107,7 @@ __global__ __launch_bounds__(NT, (xband_waves_per_simd<Q, NT, BUFS>())) void xma
   __shared__ XBand<Q, NT, BUFS> sh;
   const int n = __builtin_amdgcn_readfirstlane((int)as_global((const uint32_t*)in.counters)[in.which]);
   for (int i = threadIdx.x; i < 2 * XBand<Q, NT, BUFS>::BROWS; i += NT) sh.dirty[i & 1][i >> 1] = 0;
+  if (threadIdx.x < 2) sh.any[threadIdx.x] = 0;
   uint32_t chunks = 0;
   for (int b = blockIdx.x; b < n; b += gridDim.x) {
     const uint2 e = in.list[tile_of(b, n, order)];

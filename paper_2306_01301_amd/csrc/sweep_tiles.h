@@ -1005,6 +1005,14 @@ __device__ __forceinline__ void xmajor_sweep_tile(const SweepJob& a, int tile, X
 // are not stored.  PREF: the next chunk's band is loaded into registers while
 // the current one is scanned and stored, so each workgroup keeps loads in
 // flight through its whole loop.
+// What bounds a tile is less its bytes than the instructions and LDS waits
+// between two loads, so a section that changes nothing writes nothing back to
+// the band, and a chunk without a change has no store phase and no barrier
+// after it; what the stores need beyond the band is found only there.  512^3,
+// x-major half of a straight pass that changes nothing: 108 -> 89 us (62 us for
+// the bytes at a copy's rate); in a maze's tracked passes 105 -> 93.5 us.
+// A spilled vector register costs more than this gains: its reload waits for
+// the prefetched band.
 
 template <int Q_, int NT, int BUFS>
 struct XBand {
@@ -1027,6 +1035,7 @@ struct XBand {
   alignas(16) int16_t skew[1024];  // B(c, T) of this plane (read 8 entries at a time)
   int16_t first_col[1024];         // first column c with |B(c) - B(0)| = i (B is monotone in unit steps)
   uint8_t dirty[2][BROWS];         // band rows holding a changed value, by chunk parity
+  uint32_t any[2];                 // a band row does
   int off[4];                      // tracked sweeps: the plane's circle offsets (left x, y, right x, y)
 };
 
@@ -1147,44 +1156,6 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
   for (int k0 = 0; k0 < N; k0 += Q, buf = (BUFS == 2) ? (buf ^ 1) : 0) {
     if (!PREF) load_band(g, lv, lc);
     put_band(buf, lv, lc);
-    // groups the tile owns in part (the last lines of this tile and the
-    // first of the next, or the reverse, in one band row): a band row's
-    // owned cells run between two columns, where B(c) - bmin passes the row
-    // (first line) and the row minus t_lim (past the last line), and those
-    // lie inside the chunk only for the first brange rows after band row 0
-    // and after band row t_lim.  One lane of the last waves per such (row,
-    // edge) finds the column from the first-column table (here, so that the
-    // read overlaps the scan) and, when it falls inside a group, writes that
-    // group's owned cells one by one after the whole groups are stored; the
-    // other waves store whole groups only.
-    int pg_slot = -1;       // LDS slot of the partial group's first cell (-1: none)
-    int pg_rho = 0;         // its band row
-    uint32_t pg_rec = 0;    // its record index
-    uint32_t pg_own = 0;    // owned cells of the group, bit m for memory column gm + m
-    if (const int e = tid - (NT - 2 * Q); e >= 0) {  // (whole waves)
-      const int r = e % Q;
-      if (r < brange) {
-        const bool last = e >= Q;
-        const int rho = last ? t_lim + r : r;
-        // |B - B(0)| at the first column past the edge, in memory order
-        const int v = last ? (incr ? r + 1 + bmin - b0 : b0 - (r + bmin))
-                           : (incr ? rho + bmin + 1 - b0 : b0 - (rho + bmin));
-        const int cb = sh.first_col[v];
-        if (cb & 3) {
-          const int gm = cb & ~3;  // memory column of the group
-          int row = band_row0(bmin) + rho;
-          while (row >= N) row -= N;  // rho < BROWS: at most BROWS / N + 1 wraps
-          pg_rec = (uint32_t)row * (uint32_t)N + (uint32_t)gm;
-          pg_slot = rho * PV + (gm - (dir ? k0 : (N - k0 - Q)));
-          pg_rho = rho;
-          // the cells before cb are owned when ownership stops there (the
-          // first line's edge with B ascending, the last line's with B
-          // descending), else the cells from cb on
-          const uint32_t before = (1u << (cb & 3)) - 1u;
-          pg_own = (last != incr) ? before : (0xFu & ~before);
-        }
-      }
-    }
     BandGroup gn;
     int nq_n = 0, bmin_n = 0, brange_n = 0;
     if (PREF && k0 + Q < N) {
@@ -1208,6 +1179,7 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
     // barrier above)
     const int par = (int)(chunks & 1u);
     for (int i = tid; i < BROWS; i += NT) sh.dirty[par ^ 1][i] = 0;
+    if (tid == 0) sh.any[par ^ 1] = 0;
     uint32_t u[SUB], w[SUB];
     int soff[SUB];  // wave-uniform part of each column's value slot
     int orow[SUB];  // band row of line 0 at each column (wave-uniform)
@@ -1258,74 +1230,142 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
     sh.aggD[wave][lane] = D;
     sh.aggC[wave][lane] = C;
     __syncthreads();
+    // the value carried into this wave's section and out of the chunk, from all
+    // of the group's sections (read together: one wait)
     uint32_t v = carry;
-    for (int s = gfirst; s < wave; s++) v = umin(sadd(v, sh.aggD[s][lane]), sh.aggC[s][lane]);
-    if (wok) {
+    {
+      uint32_t sd[WPG], sc[WPG];
+#pragma unroll
+      for (int i = 0; i < WPG; i++) {
+        sd[i] = sh.aggD[gfirst + i][lane];
+        sc[i] = sh.aggC[gfirst + i][lane];
+      }
+#pragma unroll
+      for (int i = 0; i < WPG; i++) {
+        carry = umin(sadd(carry, sd[i]), sc[i]);
+        if (i + 1 == csec) v = carry;
+      }
+    }
+    // most sections change no value: only one that does writes its changed
+    // cells back to the band and flags their rows
+    uint32_t changed = 0;
+    {
+      uint32_t r = v;
+#pragma unroll
+      for (int q = 0; q < SUB; q++) {
+        changed |= (umin(r, u[q]) | (uint32_t)((int32_t)w[q] >> 31)) ^ u[q];
+        r = sadd(umin(r, sadd(u[q], a.ct)), w[q]);
+      }
+    }
+    if (wok && __builtin_amdgcn_ballot_w64(changed != 0u) != 0ull) {
       uint32_t* tVw = sh.tV[buf];
       int lpv = line * PV;
-      asm volatile("" : "+v"(lpv));  // the slots are recomputed here rather than kept from the reads (registers)
+      asm volatile("" : "+v"(lpv));  // the slots are found again rather than kept from the reads (registers)
 #pragma unroll
       for (int q = 0; q < SUB; q++) {
         const uint32_t out = umin(v, u[q]) | (uint32_t)((int32_t)w[q] >> 31);
-        tVw[lpv + soff[q]] = out;
-        // flag the band row of a changed value (most columns change none:
-        // then the wave writes no flag)
-        if (__builtin_amdgcn_ballot_w64(out != u[q]) != 0ull && out != u[q]) sh.dirty[par][line + orow[q]] = 1;
+        if (out != u[q]) {
+          tVw[lpv + soff[q]] = out;
+          sh.dirty[par][line + orow[q]] = 1;
+        }
         v = sadd(umin(v, sadd(u[q], a.ct)), w[q]);
       }
+      sh.any[par] = 1;
     }
-    for (int s = gfirst; s < gfirst + WPG; s++) carry = umin(sadd(carry, sh.aggD[s][lane]), sh.aggC[s][lane]);
     __syncthreads();
 
-    if (TRACK && tid < BROWS && sh.dirty[par][tid]) {
-      int row = band_row0(bmin) + tid;
-      while (row >= N) row -= N;
-      const int c0 = dir ? k0 : (N - k0 - nq);  // the chunk's first column in memory order
-      const GlobalPtr<uint32_t> st = as_global(a.tr.stamps);
-      stamp_circles(st, sh.off[0], sh.off[1], row, c0, nq, N, a.tr.mark_stamp);
-      stamp_circles(st + a.tiles_x * N, sh.off[2], sh.off[3], row, c0, nq, N, a.tr.mark_stamp);
-      *own_stamp(a, tile) = a.tr.own_stamp;
-    }
+    if (__builtin_amdgcn_readfirstlane((int)sh.any[par]) != 0) {  // (the same in every wave)
+      if (TRACK && tid < BROWS && sh.dirty[par][tid]) {
+        int row = band_row0(bmin) + tid;
+        while (row >= N) row -= N;
+        const int c0 = dir ? k0 : (N - k0 - nq);  // the chunk's first column in memory order
+        const GlobalPtr<uint32_t> st = as_global(a.tr.stamps);
+        stamp_circles(st, sh.off[0], sh.off[1], row, c0, nq, N, a.tr.mark_stamp);
+        stamp_circles(st + a.tiles_x * N, sh.off[2], sh.off[3], row, c0, nq, N, a.tr.mark_stamp);
+        *own_stamp(a, tile) = a.tr.own_stamp;
+      }
 
-    // store the band: a group the tile owns whole in one 16-byte store, then
-    // the owned cells of the partly owned groups found above; a band row
-    // whose values all stayed as loaded is not stored (memory holds them)
-    {
-      uint32_t pv[4];
-      if (pg_slot >= 0 && !sh.dirty[par][pg_rho]) pg_slot = -1;
-      if (pg_slot >= 0) {
-#pragma unroll
-        for (int m = 0; m < 4; m++) pv[m] = sh.tV[buf][pg_slot + m];
+      // groups the tile owns in part (the last lines of this tile and the
+      // first of the next, or the reverse, in one band row): a band row's
+      // owned cells run between two columns, where B(c) - bmin passes the row
+      // (first line) and the row minus t_lim (past the last line), and those
+      // lie inside the chunk only for the first brange rows after band row 0
+      // and after band row t_lim.  One lane of the last waves per such (row,
+      // edge) finds the column from the first-column table and, when it falls
+      // inside a group, writes that group's owned cells after the whole groups
+      // are stored; the other waves store whole groups only.
+      int pg_slot = -1;       // LDS slot of the partial group's first cell (-1: none)
+      int pg_rho = 0;         // its band row
+      uint32_t pg_rec = 0;    // its record index
+      uint32_t pg_own = 0;    // owned cells of the group, bit m for memory column gm + m
+      if (const int e = tid - (NT - 2 * Q); e >= 0) {  // (whole waves)
+        const int r = e % Q;
+        if (r < brange) {
+          const bool last = e >= Q;
+          const int rho = last ? t_lim + r : r;
+          // |B - B(0)| at the first column past the edge, in memory order
+          const int v = last ? (incr ? r + 1 + bmin - b0 : b0 - (r + bmin))
+                             : (incr ? rho + bmin + 1 - b0 : b0 - (rho + bmin));
+          const int cb = sh.first_col[v];
+          if (cb & 3) {
+            const int gm = cb & ~3;  // memory column of the group
+            int row = band_row0(bmin) + rho;
+            while (row >= N) row -= N;  // rho < BROWS: at most BROWS / N + 1 wraps
+            pg_rec = (uint32_t)row * (uint32_t)N + (uint32_t)gm;
+            pg_slot = rho * PV + (gm - (dir ? k0 : (N - k0 - Q)));
+            pg_rho = rho;
+            // the cells before cb are owned when ownership stops there (the
+            // first line's edge with B ascending, the last line's with B
+            // descending), else the cells from cb on
+            const uint32_t before = (1u << (cb & 3)) - 1u;
+            pg_own = (last != incr) ? before : (0xFu & ~before);
+          }
+        }
       }
-      const uint32_t* sv = sh.tV[buf] + r0 * PV + 4 * gs;
-      uint32_t base = g.base;
+      // store the band: a group the tile owns whole in one 16-byte store, then
+      // the owned cells of the partly owned groups found above; a band row
+      // whose values all stayed as loaded is not stored (memory holds them)
+      {
+        uint32_t pv[4];
+        if (pg_slot >= 0 && !sh.dirty[par][pg_rho]) pg_slot = -1;
+        if (pg_slot >= 0) {
 #pragma unroll
-      for (int it = 0; it < ITER; it++) {
-        if (BROWS % ROWS != 0 && r0 + it * ROWS >= BROWS) break;
-        u32x4 val;
+          for (int m = 0; m < 4; m++) pv[m] = sh.tV[buf][pg_slot + m];
+        }
+        int rs = r0;
+        asm volatile("" : "+v"(rs));
+        const uint32_t* sv = sh.tV[buf] + rs * PV + 4 * gs;
+        uint32_t base = g.base;
 #pragma unroll
-        for (int m = 0; m < 4; m++) val[m] = sv[it * ROWS * PV + m];
-        const bool all = g.ok && g.lo + it * ROWS >= 0 && g.hi + it * ROWS < t_lim;
-        if (sh.dirty[par][r0 + it * ROWS]) __builtin_amdgcn_raw_buffer_store_b128(val, rV, all ? base * 4u : kNoOffset, 0, 0);
-        base = wrap_col(base + (uint32_t)(ROWS * N), (int)NN);
+        for (int it = 0; it < ITER; it++) {
+          if (BROWS % ROWS != 0 && r0 + it * ROWS >= BROWS) break;
+          u32x4 val;
+#pragma unroll
+          for (int m = 0; m < 4; m++) val[m] = sv[it * ROWS * PV + m];
+          const bool all = g.ok && g.lo + it * ROWS >= 0 && g.hi + it * ROWS < t_lim;
+          if (sh.dirty[par][r0 + it * ROWS]) __builtin_amdgcn_raw_buffer_store_b128(val, rV, all ? base * 4u : kNoOffset, 0, 0);
+          base = wrap_col(base + (uint32_t)(ROWS * N), (int)NN);
+        }
+        if (pg_slot >= 0) {
+          // the owned cells are a run of 1 to 3 at one end of the group: one
+          // store of the run's length (each cell a separate memory request
+          // costs more than the cells' bytes)
+          const int m0 = __builtin_ctz(pg_own), len = __builtin_popcount(pg_own);
+          const uint32_t off = (pg_rec + (uint32_t)m0) * 4u;
+          const uint32_t a0 = m0 ? pv[1] : pv[0];
+          const uint32_t a1 = m0 == 0 ? pv[1] : (m0 == 1 ? pv[2] : pv[3]);
+          const uint32_t a2 = m0 ? pv[3] : pv[2];
+          typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+          typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+          if (len == 1) __builtin_amdgcn_raw_buffer_store_b32(m0 == 3 ? pv[3] : (m0 == 2 ? pv[2] : a0), rV, off, 0, 0);
+          if (len == 2) __builtin_amdgcn_raw_buffer_store_b64(u32x2{m0 ? pv[2] : pv[0], m0 ? pv[3] : pv[1]}, rV, off, 0, 0);
+          if (len == 3) __builtin_amdgcn_raw_buffer_store_b96(u32x3{a0, a1, a2}, rV, off, 0, 0);
+        }
       }
-      if (pg_slot >= 0) {
-        // the owned cells are a run of 1 to 3 at one end of the group: one
-        // store of the run's length (each cell a separate memory request
-        // costs more than the cells' bytes)
-        const int m0 = __builtin_ctz(pg_own), len = __builtin_popcount(pg_own);
-        const uint32_t off = (pg_rec + (uint32_t)m0) * 4u;
-        const uint32_t a0 = m0 ? pv[1] : pv[0];
-        const uint32_t a1 = m0 == 0 ? pv[1] : (m0 == 1 ? pv[2] : pv[3]);
-        const uint32_t a2 = m0 ? pv[3] : pv[2];
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
-        if (len == 1) __builtin_amdgcn_raw_buffer_store_b32(m0 == 3 ? pv[3] : (m0 == 2 ? pv[2] : a0), rV, off, 0, 0);
-        if (len == 2) __builtin_amdgcn_raw_buffer_store_b64(u32x2{m0 ? pv[2] : pv[0], m0 ? pv[3] : pv[1]}, rV, off, 0, 0);
-        if (len == 3) __builtin_amdgcn_raw_buffer_store_b96(u32x3{a0, a1, a2}, rV, off, 0, 0);
-      }
+      // every wave has read the band before the next chunk writes it, and
+      // the tables before the next tile does
+      if (BUFS == 1 || k0 + Q >= N) __syncthreads();
     }
-    if (BUFS == 1) __syncthreads();  // every wave has read the band before the next chunk writes it
     chunks++;
     if (PREF) {
       g = gn;

@@ -103,6 +103,40 @@ def test_straight_chunks_match_oracle(n, nt):
     p.close()
 
 
+# straight passes over volumes in which few values change: chunks and sections
+# with and without a change side by side, with one and two band buffers and with
+# workgroups that walk several tiles
+@pytest.mark.parametrize("knobs", [{}, {"xmajor_buffers": 2, "xmajor_wg_per_cu": 1}, {"xmajor_wg_per_cu": 1}])
+@pytest.mark.parametrize("n,nt", [(40, 16), (136, 24), (200, 264), (512, 128)])
+def test_sparse_changes_match_oracle(n, nt, knobs):
+    print("sparse %d x %d %s" % (n, nt, knobs), flush=True)
+    rng = np.random.default_rng(n + nt)
+    sc = scenes.random_small(n + nt, n=n, nt=nt, R=3.0, n_rect=max(2, n // 8)).with_(vehicle=(3, 1, 1))
+    prob = problem_of(sc)
+    B = oracle.render(prob, sc.image, *sc.vehicle)
+    p = P.planner_for(sc)
+    p.set_cspace(_dev(B))
+    V = rng.integers(0, 1 << 24, size=B.shape, dtype=np.uint64).astype(np.uint32)
+    V[B == HARD] = 0xFFFFFFFF
+    free = np.flatnonzero(B != HARD)
+    try:
+        for name, value in knobs.items():
+            P.set_knob(P.KNOBS[name], value)
+        for mu in (oracle.SF, oracle.SB):
+            oracle.sweep(prob, mu, B, V)
+            some = rng.choice(free, max(1, len(free) // 5000), replace=False)
+            V.reshape(-1)[some] //= 4
+            p.value.copy_(_dev(V.view(np.int32)))
+            p.sweep_one(mu)
+            oracle.sweep(prob, mu, B, V)
+            assert np.array_equal(p.value_numpy(), V)
+    finally:
+        for name in knobs:
+            P.set_knob(P.KNOBS[name], 0)
+        P.apply_tuning()
+        p.close()
+
+
 # both sides of each thread count of the back-tracking workgroups, the longest
 # curves, one maneuver and all six: a plan's cooperating workgroups against the
 # batched kernel's one, over many goals in turn (reached, unreached, the start)
