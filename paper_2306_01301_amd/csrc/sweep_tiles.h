@@ -1156,6 +1156,50 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
   for (int k0 = 0; k0 < N; k0 += Q, buf = (BUFS == 2) ? (buf ^ 1) : 0) {
     if (!PREF) load_band(g, lv, lc);
     put_band(buf, lv, lc);
+    // groups the tile owns in part (the last lines of this tile and the first
+    // of the next, or the reverse, in one band row): a band row's owned cells
+    // run between two columns, where B(c) - bmin passes the row (first line)
+    // and the row minus t_lim (past the last line), and those lie inside the
+    // chunk only for the first brange rows after band row 0 and after band row
+    // t_lim.  One lane of the last waves per such (row, edge) finds the column
+    // from the first-column table and, when it falls inside a group, writes that
+    // group's owned cells after the whole groups are stored; the other waves
+    // store whole groups only.  A launch of few wide tiles is as long as one
+    // workgroup's chain of steps: there the search is done for every chunk, where
+    // the scan hides it (200^2 x 72: 15.3 us with the search in the store phase,
+    // 14.9 here); other launches are bound by instructions and search only
+    // chunks that changed.
+    int pg_slot = -1;       // LDS slot of the partial group's first cell (-1: none)
+    int pg_rho = 0;         // its band row
+    uint32_t pg_rec = 0;    // its record index
+    uint32_t pg_own = 0;    // owned cells of the group, bit m for memory column gm + m
+    auto find_partial = [&] {
+      if (const int e = tid - (NT - 2 * Q); e >= 0) {  // (whole waves)
+        const int r = e % Q;
+        if (r < brange) {
+          const bool last = e >= Q;
+          const int rho = last ? t_lim + r : r;
+          // |B - B(0)| at the first column past the edge, in memory order
+          const int v = last ? (incr ? r + 1 + bmin - b0 : b0 - (r + bmin))
+                             : (incr ? rho + bmin + 1 - b0 : b0 - (rho + bmin));
+          const int cb = sh.first_col[v];
+          if (cb & 3) {
+            const int gm = cb & ~3;  // memory column of the group
+            int row = band_row0(bmin) + rho;
+            while (row >= N) row -= N;  // rho < BROWS: at most BROWS / N + 1 wraps
+            pg_rec = (uint32_t)row * (uint32_t)N + (uint32_t)gm;
+            pg_slot = rho * PV + (gm - (dir ? k0 : (N - k0 - Q)));
+            pg_rho = rho;
+            // the cells before cb are owned when ownership stops there (the
+            // first line's edge with B ascending, the last line's with B
+            // descending), else the cells from cb on
+            const uint32_t before = (1u << (cb & 3)) - 1u;
+            pg_own = (last != incr) ? before : (0xFu & ~before);
+          }
+        }
+      }
+    };
+    if constexpr (WPG > 4) find_partial();
     BandGroup gn;
     int nq_n = 0, bmin_n = 0, brange_n = 0;
     if (PREF && k0 + Q < N) {
@@ -1285,43 +1329,7 @@ __device__ __forceinline__ void xmajor_band_tile(const SweepJob& a, int tile, XB
         *own_stamp(a, tile) = a.tr.own_stamp;
       }
 
-      // groups the tile owns in part (the last lines of this tile and the
-      // first of the next, or the reverse, in one band row): a band row's
-      // owned cells run between two columns, where B(c) - bmin passes the row
-      // (first line) and the row minus t_lim (past the last line), and those
-      // lie inside the chunk only for the first brange rows after band row 0
-      // and after band row t_lim.  One lane of the last waves per such (row,
-      // edge) finds the column from the first-column table and, when it falls
-      // inside a group, writes that group's owned cells after the whole groups
-      // are stored; the other waves store whole groups only.
-      int pg_slot = -1;       // LDS slot of the partial group's first cell (-1: none)
-      int pg_rho = 0;         // its band row
-      uint32_t pg_rec = 0;    // its record index
-      uint32_t pg_own = 0;    // owned cells of the group, bit m for memory column gm + m
-      if (const int e = tid - (NT - 2 * Q); e >= 0) {  // (whole waves)
-        const int r = e % Q;
-        if (r < brange) {
-          const bool last = e >= Q;
-          const int rho = last ? t_lim + r : r;
-          // |B - B(0)| at the first column past the edge, in memory order
-          const int v = last ? (incr ? r + 1 + bmin - b0 : b0 - (r + bmin))
-                             : (incr ? rho + bmin + 1 - b0 : b0 - (rho + bmin));
-          const int cb = sh.first_col[v];
-          if (cb & 3) {
-            const int gm = cb & ~3;  // memory column of the group
-            int row = band_row0(bmin) + rho;
-            while (row >= N) row -= N;  // rho < BROWS: at most BROWS / N + 1 wraps
-            pg_rec = (uint32_t)row * (uint32_t)N + (uint32_t)gm;
-            pg_slot = rho * PV + (gm - (dir ? k0 : (N - k0 - Q)));
-            pg_rho = rho;
-            // the cells before cb are owned when ownership stops there (the
-            // first line's edge with B ascending, the last line's with B
-            // descending), else the cells from cb on
-            const uint32_t before = (1u << (cb & 3)) - 1u;
-            pg_own = (last != incr) ? before : (0xFu & ~before);
-          }
-        }
-      }
+      if constexpr (WPG <= 4) find_partial();
       // store the band: a group the tile owns whole in one 16-byte store, then
       // the owned cells of the partly owned groups found above; a band row
       // whose values all stayed as loaded is not stored (memory holds them)
