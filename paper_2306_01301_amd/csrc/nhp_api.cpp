@@ -186,6 +186,18 @@ int nhp::track_plan(nhp_plan* plan, hipStream_t stream) {
   return NHP_OK;
 }
 
+// A captured launch may run at any later time, or never, so what is known of
+// the volumes ends with it: the sweep is captured in full, and later sweeps that
+// go on from the volume start in full, as after the caller's own writes.
+bool nhp::captured(nhp_plan* plan, hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();  // (left for the launch to report)
+  if (st == hipStreamCaptureStatusNone) return false;
+  plan->exposed = true;
+  plan->ts_valid = false;
+  return true;
+}
+
 // The plan's two areas of exchange words take turns: an extraction clears the
 // one that the next takes, so a clearing launch is needed only before the first
 // and after one that did not run to its end (finish_extract sets ex_clear).
@@ -473,7 +485,7 @@ static hipGraphExec_t capture_passes(nhp_plan* plan, const std::vector<nhp::Pass
 static int run_cycles(nhp_plan* plan, uint32_t n_cycles) {
   const bool pairs = nhp::can_fuse(plan->d);
   nhp::TrackState* ts = nullptr;
-  if (nhp::track_sweeps(plan->d) && (plan->ts_valid || n_cycles > 1)) {
+  if (!nhp::captured(plan, plan->stream) && nhp::track_sweeps(plan->d) && (plan->ts_valid || n_cycles > 1)) {
     int rc = nhp::track_plan(plan, plan->stream);
     if (rc) return rc;
     ts = &plan->ts;
@@ -569,6 +581,7 @@ int sweep_pass(nhp_plan* plan, int32_t first, int32_t second) {
   if (!plan->has_cspace) return fail(NHP_ESTATE, "sweep_pass before render_cspace/plan_set_cspace");
   if (first < 0 || first > 5 || second < -1 || second > 5) return fail(NHP_EINVAL, "maneuvers must be 0..5 (second: -1 for none)");
   plan->ts_valid = false;
+  (void)nhp::captured(plan, plan->stream);
   HIP_CHECK(nhp::launch_sweep(plan->d, nhp::Pass{(int8_t)first, (int8_t)second}, plan->stream), "sweep launch");
   return ok();
 }
@@ -580,6 +593,7 @@ int sweep_straight_family(nhp_plan* plan, uint32_t maneuver, uint32_t family) {
   if (maneuver != NHP_SF && maneuver != NHP_SB) return fail(NHP_EINVAL, "maneuver must be NHP_SF or NHP_SB");
   if (family > 1) return fail(NHP_EINVAL, "family must be 0 or 1");
   plan->ts_valid = false;
+  (void)nhp::captured(plan, plan->stream);
   HIP_CHECK(nhp::launch_sweep_part(plan->d, nhp::Pass{(int8_t)maneuver, (int8_t)-1}, family ? 1 : 2, plan->stream),
             "sweep launch");
   return ok();
@@ -608,6 +622,7 @@ int sweep_one(nhp_plan* plan, uint32_t maneuver) {
   if (!plan->has_cspace) return fail(NHP_ESTATE, "sweep_one before render_cspace/plan_set_cspace");
   if (maneuver > 5) return fail(NHP_EINVAL, "maneuver must be 0..5");
   plan->ts_valid = false;
+  (void)nhp::captured(plan, plan->stream);
   HIP_CHECK(nhp::launch_sweep(plan->d, nhp::Pass{(int8_t)maneuver, (int8_t)-1}, plan->stream), "sweep launch");
   return ok();
 }

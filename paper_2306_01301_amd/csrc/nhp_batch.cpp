@@ -488,7 +488,10 @@ static int advance(nhp_batch* b, nhp_plan* const* plans, const uint32_t* steps, 
   std::vector<nhp::Pass> now;
   std::vector<nhp::SweepJob> table;
   std::vector<Launch> launches;
-  const bool track = track_batch(plans, counts, n);
+  bool capture = false;
+  for (uint32_t k = 0; k < n; k++)
+    if (counts[k] > 0) capture = nhp::captured(plans[k], b->stream) || capture;
+  const bool track = !capture && track_batch(plans, counts, n);
   for (uint32_t k = 0; k < n; k++) {
     if (passes[k].empty()) continue;
     if (track && (rc = nhp::track_plan(plans[k], b->stream))) return rc;

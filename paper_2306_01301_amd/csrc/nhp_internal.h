@@ -377,6 +377,7 @@ int set_error(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3
 int clear_error();
 StartTiles start_tiles(const nhp_plan* plan, int i, int j, int T);
 void track_restart(nhp_plan* plan);
+bool captured(nhp_plan* plan, hipStream_t stream);
 int track_plan(nhp_plan* plan, hipStream_t stream);
 int upload_taps(nhp_plan* plan, int front, int rear, int half_width);
 // Checks a vehicle box; the sample offsets of all planes then take

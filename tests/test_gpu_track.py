@@ -199,3 +199,31 @@ def test_tracked_resume_of_a_volume_nobody_has_seen():
     _same(q, want, "resume after single passes")
     p.close()
     q.close()
+
+
+def test_captured_sweeps_between_eager_ones():
+    """A sweep captured into a graph, not run, then run after other sweeps:
+    every sweep goes on from what the volume holds when it runs."""
+    sc = _scene(512, 256, 5, FULL)
+    stream = torch.cuda.Stream()
+    p = P.planner_for(sc, stream=stream)
+    with torch.cuda.stream(stream):
+        image = torch.from_numpy(sc.image).cuda()
+    p.render(image, sc.vehicle)
+    p.sweep(sc.start, 2)
+    graph = torch.cuda.CUDAGraph()
+    print("capture", flush=True)
+    with torch.cuda.graph(graph, stream=stream):
+        p.resume(1)
+    p.resume(1)
+    with torch.cuda.stream(stream):
+        graph.replay()
+    p.resume(1)
+    stream.synchronize()
+    got = p.value.clone()
+    torch.cuda.synchronize()  # (the copy is on another stream than the plan's)
+    p.sweep(sc.start, 0)
+    _passes(p, FULL, 5)
+    stream.synchronize()
+    assert torch.equal(got, p.value)
+    p.close()
