@@ -232,7 +232,7 @@ int extract_path(nhp_plan* plan, uint32_t gi, uint32_t gj, uint32_t gt, uint32_t
  * arguments, results and errors, but this call allocates nothing, neither
  * device nor pinned host memory.  Its extract area (result header, the step
  * list of up to NHP_MAX_STEPS_DEVICE steps, the back-tracking kernel's
- * barrier counter and exchange words: NHP_NOALLOC_EXTRACT_BYTES bytes) is a
+ * exchange words: NHP_NOALLOC_EXTRACT_BYTES bytes) is a
  * fixed device array of the library, one per GPU, held until the process
  * ends; its size does not depend on the grid, so every plan fits (a walk
  * longer than NHP_MAX_STEPS_DEVICE steps is NHP_EUNREACH, as in
