@@ -483,6 +483,7 @@ static hipGraphExec_t capture_passes(nhp_plan* plan, const std::vector<nhp::Pass
 // A plan whose sweeps are tracked launches its kernels directly: their
 // arguments carry the pass numbers.
 static int run_cycles(nhp_plan* plan, uint32_t n_cycles) {
+  if (n_cycles == 0) return NHP_OK;  // (the stamps know as much, or as little, as before)
   const bool pairs = nhp::can_fuse(plan->d);
   nhp::TrackState* ts = nullptr;
   if (!nhp::captured(plan, plan->stream) && nhp::track_sweeps(plan->d) && (plan->ts_valid || n_cycles > 1)) {
@@ -507,7 +508,7 @@ static int run_cycles(nhp_plan* plan, uint32_t n_cycles) {
     }
     skip = consumed;
   }
-  plan->ts_valid = ts != nullptr || n_cycles == 0;
+  plan->ts_valid = ts != nullptr;
   return NHP_OK;
 }
 

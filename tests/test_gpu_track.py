@@ -227,3 +227,39 @@ def test_captured_sweeps_between_eager_ones():
     stream.synchronize()
     assert torch.equal(got, p.value)
     p.close()
+
+
+# ---- what is known of a volume when a call goes on from it ----
+
+@pytest.mark.parametrize("how", ["one plan", "batch"])
+def test_zero_cycle_resume_knows_no_more_than_before(how):
+    """resume(0) after passes that kept no record of their changes."""
+    if how == "one plan":
+        # a maze, in which every cycle still reaches new poses
+        sc = _scene(512, 256, 11, FULL).with_(image=scenes.maze(np.random.default_rng(11), 16, 32, 4), start=(18, 18, 0))
+        want = _in_full([sc], [9])[0]
+        p = P.planner_for(sc)
+        p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+        p.sweep(sc.start, 7)
+        for mu in FULL:
+            p.sweep_one(mu)
+        p.resume(0)
+        p.resume(1)
+        _same(p, want, "resume")
+        p.close()
+        return
+    scs = [_scene(256, 256, 20 + k, FULL) for k in range(4)]
+    want = _in_full(scs, [5] * 4)
+    ps = [P.planner_for(sc) for sc in scs]
+    for p, sc in zip(ps, scs):
+        p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+        p.sweep(sc.start, 3)
+        p.resume(0)
+    torch.cuda.synchronize()
+    b = P.Batch(4)
+    b.advance(ps, [18] * 4, [12] * 4)
+    for p, w in zip(ps, want):
+        _same(p, w, "batch")
+    b.close()
+    for p in ps:
+        p.close()
