@@ -262,7 +262,8 @@ int extract_path_set(nhp_plan* plan, const uint32_t* goals_ijt, const uint32_t* 
  * checks and checkpoints; owned by the plan).  Either output may be NULL.
  * The caller may write the volumes between calls: a plan whose pointers have
  * been asked for has sweep_resume and batch_advance visit every tile again
- * (others go on from what their last call left). */
+ * (others go on from what their last call left).  The same holds for a plan
+ * that a captured call writes, as its graph may run between any two calls. */
 int plan_device_ptrs(const nhp_plan* plan, uint32_t** d_value, uint8_t** d_cspace);
 
 /* Copies the host tables out (each host array may be NULL):
@@ -283,6 +284,9 @@ int plan_get_tables(const nhp_plan* plan, int32_t* beta, int32_t* psi, int32_t* 
  * other streams must be complete.  A plan may appear once per call.  Job
  * tables live in a ring of 4 pinned/device buffer pairs owned by the batch;
  * a call waits only when it reuses a buffer whose launches are still queued.
+ * A replay of a captured batch call reads the call's buffer again, and a
+ * captured buffer cannot be reused: capture at most 4 calls of a batch, and
+ * make no others on it from then on.
  * Every entry point returns a status; plan_last_error() explains failures.
  * ------------------------------------------------------------------------ */
 typedef struct nhp_batch nhp_batch;

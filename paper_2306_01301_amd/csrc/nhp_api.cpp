@@ -187,8 +187,9 @@ int nhp::track_plan(nhp_plan* plan, hipStream_t stream) {
 }
 
 // A captured launch may run at any later time, or never, so what is known of
-// the volumes ends with it: the sweep is captured in full, and later sweeps that
-// go on from the volume start in full, as after the caller's own writes.
+// the volumes ends with it: a sweep is captured in full, and later sweeps that go
+// on from the volume start in full, as after the caller's own writes.  Every
+// entry point that can be captured and writes a volume asks this first.
 bool nhp::captured(nhp_plan* plan, hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();  // (left for the launch to report)
@@ -362,6 +363,7 @@ int render_cspace(nhp_plan* plan, const uint8_t* d_image, int32_t front, int32_t
   const int n_side = 2 * half_width + 1, n_len = front + rear + 1;
   rc = nhp::upload_taps(plan, front, rear, half_width);
   if (rc) return rc;
+  (void)nhp::captured(plan, plan->stream);
   HIP_CHECK(nhp::launch_render(plan->d, d_image, n_side, n_len, plan->stream), "render_cspace launch");
   plan->has_cspace = true;
   plan->has_value = false;
@@ -430,6 +432,7 @@ int plan_set_cspace(nhp_plan* plan, const uint8_t* d_cspace) {
   if (rc) return rc;
   if (!d_cspace) return fail(NHP_EINVAL, "cspace is NULL");
   const size_t NR = (size_t)plan->p.nx * plan->p.nx * plan->p.ntheta;
+  (void)nhp::captured(plan, plan->stream);
   HIP_CHECK(hipMemcpyAsync(plan->d.B, d_cspace, NR, hipMemcpyDeviceToDevice, plan->stream), "cspace copy");
   HIP_CHECK(nhp::launch_force_walls(plan->d, plan->stream), "wall launch");
   plan->has_cspace = true;

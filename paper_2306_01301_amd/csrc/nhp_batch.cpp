@@ -202,6 +202,7 @@ int batch_render(nhp_batch* b, nhp_plan* const* plans, const uint8_t* const* d_i
     job.pad_first = pad_rows;
     pad_rows += job.N;
   }
+  for (uint32_t k = 0; k < n; k++) (void)nhp::captured(plans[k], b->stream);
   const size_t job_bytes = (jobs.size() * sizeof(nhp::RenderJob) + 255) & ~(size_t)255;
   Slot* s;
   rc = take_slot(b, job_bytes + tap_words * 4, &s);
@@ -539,7 +540,10 @@ int batch_step(nhp_batch* b, nhp_plan* const* plans, const uint32_t* steps, uint
   }
   std::vector<nhp::SweepJob> table;
   std::vector<Launch> launches;
-  for (uint32_t k = 0; k < n; k++) plans[k]->ts_valid = false;
+  for (uint32_t k = 0; k < n; k++) {
+    (void)nhp::captured(plans[k], b->stream);
+    plans[k]->ts_valid = false;
+  }
   rc = add_pass(plans, now.data(), n, false, table, launches);
   if (!rc) rc = run_launches(b, table, launches, false);
   return rc ? rc : nhp::clear_error();

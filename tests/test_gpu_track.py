@@ -263,3 +263,42 @@ def test_zero_cycle_resume_knows_no_more_than_before(how):
     b.close()
     for p in ps:
         p.close()
+
+
+@pytest.mark.parametrize("kind", ["set_cspace", "render", "batch render", "batch step"])
+def test_captured_changes_between_eager_sweeps(kind):
+    """A call that changes a plan's volumes, captured into a graph and run
+    between two sweeps: the second goes on from what the volumes then hold."""
+    sc = _scene(512, 256, 7, FULL)
+    stream = torch.cuda.Stream()
+    p, q = P.planner_for(sc, stream=stream), P.planner_for(sc, stream=stream)
+    batches = {p: P.Batch(1, stream=stream), q: P.Batch(1, stream=stream)}
+    with torch.cuda.stream(stream):
+        image, clear = torch.from_numpy(sc.image).cuda(), torch.zeros(512, 512, dtype=torch.uint8, device="cuda")
+        codes = torch.zeros(sc.nt, sc.nx, sc.nx, dtype=torch.uint8, device="cuda")
+    change = {"set_cspace": lambda x: x.set_cspace(codes), "render": lambda x: x.render(clear, sc.vehicle),
+              "batch render": lambda x: batches[x].render([x], [clear], [sc.vehicle]),
+              "batch step": lambda x: [batches[x].step([x], [k]) for k in range(4)]}[kind]
+    # what it comes to, every pass in full
+    q.render(image, sc.vehicle)
+    q.sweep(sc.start, 0)
+    _passes(q, FULL, 7)
+    change(q)
+    _passes(q, FULL, 1)
+    p.render(image, sc.vehicle)
+    p.sweep(sc.start, 1)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    print("capture", kind, flush=True)
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="relaxed"):
+        change(p)
+    p.render(image, sc.vehicle)
+    p.sweep(sc.start, 7)
+    with torch.cuda.stream(stream):
+        graph.replay()
+    p.resume(1)
+    stream.synchronize()
+    assert torch.equal(p.value, q.value), int((p.value != q.value).sum())
+    for x in (p, q):
+        batches[x].close()
+        x.close()
