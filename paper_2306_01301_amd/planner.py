@@ -406,7 +406,9 @@ class Planner:
         _check(lib().plan_set_stream(self._plan, ctypes.c_void_p(stream.cuda_stream)), "plan_set_stream")
 
     def close(self) -> None:
+        """Frees the plan; the views of its volumes stay (the workspace is the planner's)."""
         if getattr(self, "_plan", None) is not None and self._plan.value:
+            self._volume_offsets()
             lib().plan_destroy(self._plan)
             self._plan = ctypes.c_void_p()
 

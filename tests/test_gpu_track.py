@@ -302,3 +302,19 @@ def test_captured_changes_between_eager_sweeps(kind):
     for x in (p, q):
         batches[x].close()
         x.close()
+
+
+def test_views_of_a_closed_planner():
+    """The volumes are in the planner's own workspace: its views outlive the plan."""
+    sc = _scene(64, 64, 3, FULL)
+    out = []
+    for look_first in (True, False):
+        p = P.planner_for(sc)
+        p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+        p.sweep(sc.start, 2)
+        if look_first:
+            p.value, p.cspace
+        p.close()
+        out.append((p.value_numpy().copy(), p.cspace_numpy().copy()))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    assert out[0][0].min() == 0 and out[0][1].max() == 255
