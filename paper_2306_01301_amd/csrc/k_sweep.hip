@@ -338,10 +338,10 @@ hipError_t launch_init(const DevPlan& d, uint32_t start_index, const StartTiles&
   return hipGetLastError();
 }
 
-hipError_t launch_clear_stamps(const DevPlan& d, hipStream_t s) {
+hipError_t launch_clear(uint32_t* words, size_t n, hipStream_t s) {
   InitJob j{};
-  j.stamps = d.stamps;
-  j.n_stamps = (uint32_t)stamp_layout(d.nx, d.nt).words;
+  j.stamps = words;
+  j.n_stamps = (uint32_t)n;
   for (uint32_t& m : j.marked) m = kNoTile;
   hipLaunchKernelGGL(init_kernel, dim3((j.n_stamps + 255) / 256), dim3(256), 0, s, j);
   return hipGetLastError();

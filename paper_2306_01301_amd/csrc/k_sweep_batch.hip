@@ -26,7 +26,12 @@ __global__ __launch_bounds__(256) void list_tiles_kernel(const SweepJob* __restr
   __syncthreads();
   uint32_t p = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
   for (int w = 0; w < wave; w++) p += count[w];
-  if (on) out.list[p] = make_uint2((uint32_t)tile, (uint32_t)j);
+  if (on && p < out.room) out.list[p] = make_uint2((uint32_t)tile, (uint32_t)j);
+}
+
+__device__ __forceinline__ int listed_tiles(const TileLists& in) {
+  const uint32_t n = as_global((const uint32_t*)in.counters)[in.which];
+  return __builtin_amdgcn_readfirstlane((int)umin(n, in.room));
 }
 
 // Listed tiles of a tracked batched launch (row_track_kernel over many jobs).
@@ -37,7 +42,7 @@ __global__ __launch_bounds__(1024) void row_track_batch_kernel(const SweepJob* _
   __shared__ RowShared sh;
   __shared__ StepStore<P, LDS> store;
   StepKeep<P, LDS> keep(store);
-  const int n = __builtin_amdgcn_readfirstlane((int)as_global((const uint32_t*)in.counters)[in.which]);
+  const int n = listed_tiles(in);
   int jg = -1;     // job whose tile was swept last, and whose geometry is kept
   int swept = -1;  // that tile, if its changes are still to be stamped
   int parity = 0;
@@ -105,7 +110,7 @@ template <int Q, int NT, int BUFS>
 __global__ __launch_bounds__(NT, (xband_waves_per_simd<Q, NT, BUFS>())) void xmajor_track_batch_kernel(
     const SweepJob* __restrict__ jobs, TileLists in, int order) {
   __shared__ XBand<Q, NT, BUFS> sh;
-  const int n = __builtin_amdgcn_readfirstlane((int)as_global((const uint32_t*)in.counters)[in.which]);
+  const int n = listed_tiles(in);
   for (int i = threadIdx.x; i < 2 * XBand<Q, NT, BUFS>::BROWS; i += NT) sh.dirty[i & 1][i >> 1] = 0;
   if (threadIdx.x < 2) sh.any[threadIdx.x] = 0;
   uint32_t chunks = 0;

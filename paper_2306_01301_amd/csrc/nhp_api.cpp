@@ -179,7 +179,7 @@ void nhp::track_restart(nhp_plan* plan) {
 // visits all tiles.
 int nhp::track_plan(nhp_plan* plan, hipStream_t stream) {
   if (plan->ts_valid && plan->ts.pass < (1u << 30)) return NHP_OK;
-  HIP_CHECK(launch_clear_stamps(plan->d, stream), "stamp launch");
+  HIP_CHECK(launch_clear(plan->d.stamps, stamp_layout(plan->d.nx, plan->d.nt).words, stream), "stamp launch");
   plan->ts = TrackState{};
   for (uint32_t& q : plan->ts.last) q = kTrackStale;
   plan->ts_valid = true;

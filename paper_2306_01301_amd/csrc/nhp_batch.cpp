@@ -60,15 +60,18 @@ struct nhp_batch {
   int seen_next = 0;
   uint64_t clock = 0;
   bool graph_failed = false;  // capture unavailable: launch directly
-  // tracked launches: the tiles to visit, and the two counters in front of them
+  // tracked launches: the tiles to visit, and the two counters in front of them.
+  // A launch counts from where the one before it cleared, so after new memory, or
+  // calls that did not launch all they meant to, the counters are cleared first.
   void* lists = nullptr;
   size_t list_tiles = 0;
   int which = 0;
+  bool counters_known = false;
 };
 
 namespace {
 
-// Room for the list of a launch of `tiles` tiles.  The counters start at zero.
+// Room for the list of a launch of `tiles` tiles.
 int take_lists(nhp_batch* b, size_t tiles) {
   if (tiles <= b->list_tiles) return NHP_OK;
   const size_t n = std::max(tiles + tiles / 4, (size_t)16384);
@@ -76,11 +79,9 @@ int take_lists(nhp_batch* b, size_t tiles) {
   if (b->lists) (void)hipFree(b->lists);
   b->lists = nullptr;
   b->list_tiles = 0;
+  b->counters_known = false;
   HIP_TRY(hipMalloc(&b->lists, 256 + n * sizeof(uint2)), "hipMalloc");
-  const uint32_t zero[2] = {0, 0};
-  HIP_TRY(hipMemcpy(b->lists, zero, sizeof(zero), hipMemcpyHostToDevice), "list counters");
   b->list_tiles = n;
-  b->which = 0;
   return NHP_OK;
 }
 
@@ -339,6 +340,7 @@ static hipError_t enqueue_launches(const nhp::SweepJob* d, const std::vector<Lau
     if (tracked) {
       lists.counters = static_cast<uint32_t*>(tracked->lists);
       lists.list = reinterpret_cast<uint2*>(static_cast<char*>(tracked->lists) + 256);
+      lists.room = (uint32_t)tracked->list_tiles;
       lists.which = tracked->which;
       tracked->which ^= 1;
     }
@@ -398,7 +400,10 @@ static int run_launches(nhp_batch* b, const std::vector<nhp::SweepJob>& table, c
     memcpy(s->host, table.data(), table.size() * sizeof(nhp::SweepJob));
     HIP_TRY(hipMemcpyAsync(s->dev, s->host, table.size() * sizeof(nhp::SweepJob), hipMemcpyHostToDevice, b->stream),
             "job upload");
+    if (!b->counters_known) HIP_TRY(nhp::launch_clear(static_cast<uint32_t*>(b->lists), 2, b->stream), "list counters");
+    b->counters_known = false;
     HIP_TRY(enqueue_launches(reinterpret_cast<const nhp::SweepJob*>(s->dev), launches, b, b->stream), "sweep launch");
+    b->counters_known = true;
     return finish_slot(b, s);
   }
   std::vector<unsigned char> key(nhp::kKnobs * sizeof(int32_t) + table.size() * sizeof(nhp::SweepJob) +

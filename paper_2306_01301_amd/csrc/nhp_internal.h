@@ -209,6 +209,7 @@ int xmajor_lines(int N);  // lines per x-major tile
 struct TileLists {
   uint2* list;         // (tile, job) of every tile to visit; room for the launch's blocks
   uint32_t* counters;  // two: the launches take turns, each clears the other's
+  uint32_t room;       // tiles the list holds
   int which;
 };
 hipError_t launch_sweep_batch(const SweepJob* d_jobs, int n_jobs, int total_blocks, int P, bool fused, bool guard,
@@ -240,8 +241,8 @@ struct StartTiles {
   uint32_t t[3];
 };
 hipError_t launch_init(const DevPlan& d, uint32_t start_index, const StartTiles& marked, hipStream_t s);
-// Every stamp 0.
-hipError_t launch_clear_stamps(const DevPlan& d, hipStream_t s);
+// n words 0.
+hipError_t launch_clear(uint32_t* words, size_t n, hipStream_t s);
 hipError_t launch_force_walls(const DevPlan& d, hipStream_t s);
 hipError_t launch_sweep(const DevPlan& d, Pass pass, hipStream_t s, TrackState* ts = nullptr);
 // Part of a pass: parts bit 0 = the row kernel (turn curves, or the y-major

@@ -1,0 +1,34 @@
+"""The library's host side without a GPU: tests/host/sweep_routes.cpp compiles
+it over a runtime that launches nothing and notes what it is asked to launch."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2306_01301_amd import build as hip_build
+from paper_2306_01301_amd import planner as P
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host") / "sweep_routes")
+    src = [os.path.join(HERE, "host", "sweep_routes.cpp")] + [
+        os.path.join(hip_build.CSRC, f) for f in ("nhp_api.cpp", "nhp_batch.cpp", "nhp_tables.cpp")]
+    subprocess.check_call([CLANG, "-x", "c++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                           "-I" + hip_build.INCLUDE, "-I" + hip_build.CSRC] + src + ["-o", exe])
+
+    def run(what):
+        out = subprocess.run([exe, what], capture_output=True, text=True, timeout=60)
+        assert out.returncode == 0, out.stdout + out.stderr
+        return dict(line.split(": ", 1) for line in out.stdout.splitlines())
+
+    return run
+
+
+def test_a_failed_launch_leaves_no_tiles_in_the_next_list(ask):
+    got = ask("failed_list_launch")
+    assert got.pop("wrong") == "nothing"
+    assert got == {"failure at launch %d" % k: "t %d 0 t" % P.EHIP for k in range(6)}
