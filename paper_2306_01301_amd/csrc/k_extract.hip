@@ -219,8 +219,7 @@ __global__ __launch_bounds__(kThreads) void seed_kernel(DevPlan d) {
 // words, no counter and no cache maintenance is needed: the tables and volumes,
 // which nothing writes meanwhile, stay cached from step to step.  A workgroup
 // is at most one step ahead of another, whose words of the step before are in
-// the other buffer.  Polls are bounded.
-constexpr uint32_t kMaxPolls = 1u << 22;
+// the other buffer.  Polls are bounded (kMaxPolls).
 constexpr int kExchangeWords = 2 * 6 * 2;  // 64-bit words: parities, slots, words
 static_assert(2 * kExchangeWords == kExSyncWords, "the extract area's words after the steps");
 __device__ __forceinline__ uint64_t step_tag(uint32_t iter) { return (uint64_t)(1u + (iter >> 1) % 3u) << 62; }
@@ -576,6 +575,7 @@ __device__ __forceinline__ void extract_group(const ExArgs& x, uint32_t (*red32)
         const uint64_t* p = words + (iter & 1u) * 12u + (uint32_t)tid;
         uint32_t polls = 0;
         do {
+          if (polls >= kFastPolls) __builtin_amdgcn_s_sleep(kPollPause);
           v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } while ((v & (3ull << 62)) != step_tag(iter) && ++polls < kMaxPolls);
       }

@@ -227,6 +227,14 @@ constexpr int kExSyncWords = 2 * 6 * 4;
 constexpr size_t kExAreaWords = kExHeader + (size_t)NHP_MAX_STEPS_DEVICE * kExStepWords;  // words before them
 constexpr size_t kExPlanWords = kExAreaWords + 2 * kExSyncWords;
 static_assert(kExAreaWords % 2 == 0 && kExSyncWords % 2 == 0, "64-bit words");
+// Wait of the back-tracking workgroups for one another: kFastPolls reads in a
+// row (a step of workgroups that run side by side ends within a few), then a
+// pause of kPollPause times 64 clocks before each, and after kMaxPolls NHP_EHIP.
+// Workgroups that other streams' kernels keep from running together are so waited
+// for for at least 14 s (at 2.4 GHz).
+constexpr uint32_t kFastPolls = 1u << 12, kMaxPolls = 1u << 24;
+constexpr int kPollPause = 32;
+constexpr uint64_t kLeastWaitClocks = (uint64_t)(kMaxPolls - kFastPolls) * kPollPause * 64;
 // seed entry: pose index (kNoSeed when unused), value, start index, edges along its maneuver
 constexpr int kSeedWords = 4;
 constexpr uint32_t kNoSeed = 0xFFFFFFFFu;

@@ -202,11 +202,14 @@ void failed_list_launch() {
   for (nhp_plan* p : plan) plan_destroy(p);
 }
 
+void extract_wait() { printf("milliseconds at 2.4 GHz: %llu\n", (unsigned long long)(nhp::kLeastWaitClocks / 2400000)); }
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "failed_list_launch") failed_list_launch();
+  if (what == "extract_wait") extract_wait();
   printf("wrong: %s\n", g_wrong.empty() ? "nothing" : g_wrong.c_str());
   return 0;
 }

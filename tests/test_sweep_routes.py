@@ -32,3 +32,9 @@ def test_a_failed_launch_leaves_no_tiles_in_the_next_list(ask):
     got = ask("failed_list_launch")
     assert got.pop("wrong") == "nothing"
     assert got == {"failure at launch %d" % k: "t %d 0 t" % P.EHIP for k in range(6)}
+
+
+def test_back_tracking_waits_for_workgroups_that_start_late(ask):
+    # six workgroups wait for one another; long kernels of other streams may
+    # hold some of them up for seconds
+    assert int(ask("extract_wait")["milliseconds at 2.4 GHz"]) >= 14000
