@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <chrono>
 #include <map>
 #include <string>
 #include <vector>
@@ -202,6 +203,37 @@ void failed_list_launch() {
   for (nhp_plan* p : plan) plan_destroy(p);
 }
 
+double now() { return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count(); }
+
+// A call that repeats an earlier one against hashing the bytes of its job table
+// one by one, the fastest of 20 each.
+void repeated_call() {
+  constexpr int kPlans = 256;
+  std::vector<nhp_plan*> plan(kPlans);
+  std::vector<uint32_t> start(3 * kPlans, 5), steps(kPlans, 0), counts(kPlans, 6);
+  for (nhp_plan*& p : plan) p = make_plan(32, 16);
+  nhp_batch* b = nullptr;
+  batch_create(kPlans, nullptr, &b);
+  batch_init(b, plan.data(), start.data(), kPlans);
+  double call = 1e9, bytes = 1e9;
+  std::vector<unsigned char> table(kPlans * 6 * sizeof(nhp::SweepJob), 1);
+  volatile uint64_t sink = 0;
+  for (int k = 0; k < 20; k++) {
+    double t = now();
+    batch_advance(b, plan.data(), steps.data(), counts.data(), kPlans);
+    call = std::min(call, now() - t);
+    t = now();
+    uint64_t h = 1469598103934665603ull;
+    for (unsigned char c : table) h = (h ^ c) * 1099511628211ull;
+    bytes = std::min(bytes, now() - t);
+    sink = sink + h;
+  }
+  printf("route: %c\nfaster than its table's bytes: %s\n", route(), call < bytes ? "yes" : "no");
+  fprintf(stderr, "call %.1f us, bytes %.1f us\n", call * 1e6, bytes * 1e6);
+  batch_destroy(b);
+  for (nhp_plan* p : plan) plan_destroy(p);
+}
+
 void extract_wait() { printf("milliseconds at 2.4 GHz: %llu\n", (unsigned long long)(nhp::kLeastWaitClocks / 2400000)); }
 
 }  // namespace
@@ -210,6 +242,7 @@ int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "failed_list_launch") failed_list_launch();
   if (what == "extract_wait") extract_wait();
+  if (what == "repeated_call") repeated_call();
   printf("wrong: %s\n", g_wrong.empty() ? "nothing" : g_wrong.c_str());
   return 0;
 }

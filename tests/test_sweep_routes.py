@@ -38,3 +38,10 @@ def test_back_tracking_waits_for_workgroups_that_start_late(ask):
     # six workgroups wait for one another; long kernels of other streams may
     # hold some of them up for seconds
     assert int(ask("extract_wait")["milliseconds at 2.4 GHz"]) >= 14000
+
+
+def test_a_repeated_shared_call_is_found_by_words(ask):
+    # 256 plans of 32^2 x 16: looking the launches up must not take longer than
+    # going through the job table byte by byte
+    got = ask("repeated_call")
+    assert got["route"] == "f" and got["faster than its table's bytes"] == "yes"
