@@ -262,7 +262,7 @@ int extract_path_set(nhp_plan* plan, const uint32_t* goals_ijt, const uint32_t* 
  * checks and checkpoints; owned by the plan).  Either output may be NULL.
  * The caller may write the volumes between calls: a plan whose pointers have
  * been asked for has sweep_resume and batch_advance visit every tile again
- * (others go on from what their last call left).  The same holds for a plan
+ * (others may go on from what their last call left).  The same holds for a plan
  * that a captured call writes, as its graph may run between any two calls. */
 int plan_device_ptrs(const nhp_plan* plan, uint32_t** d_value, uint8_t** d_cspace);
 
@@ -314,9 +314,12 @@ int batch_init(nhp_batch* batch, nhp_plan* const* plans, const uint32_t* starts_
 int batch_step(nhp_batch* batch, nhp_plan* const* plans, const uint32_t* steps, uint32_t n);
 
 /* Several ticks at once: plan k runs its sweeps steps[k] .. steps[k] +
- * counts[k] - 1 (counts[k] = 0: none).  Calls over at least 2^24 poses
- * (plans with counts[k] > 0, all of side 32 or more) visit only the tiles
- * that changes have reached.  A smaller call whose launches repeat those of
+ * counts[k] - 1 (counts[k] = 0: none).  Calls over at least 2^26 poses
+ * (plans with counts[k] > 0, all of side 32 or more), or 2^24 when 6 cycles
+ * went this way before, visit only the tiles that changes have reached, if
+ * that is known of every plan: one whose volumes' addresses were handed out,
+ * or that was last swept by a call that visits all tiles, ends it for the
+ * whole call.  Any other call whose launches repeat those of
  * an earlier call on this batch (the same plans at the same points of their
  * schedules, under the same knobs) is captured into a HIP graph the second
  * time and replayed after that; the batch keeps up to 16 such graphs, each

@@ -222,6 +222,7 @@ int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj, 
   const StampLayout sl = stamp_layout(N, L);
   if (ts) {
     const uint32_t p = ++ts->pass;
+    ts->sweeps += pass.mu2 >= 0 ? 2 : 1;
     // visit what changed since either maneuver's last pass
     uint32_t last = ts->last[mu];
     if (pass.mu2 >= 0 && last != kTrackStale) {

@@ -476,21 +476,38 @@ static int run_launches(nhp_batch* b, const std::vector<nhp::SweepJob>& table, c
   return finish_slot(b, s);
 }
 
-// Tracking pays in shared launches of at least 2^24 poses, whatever the size of
-// the plans in them: the tiles are listed by one more launch of 5 us, against
-// launches of 100 us and more (60 plans of sides 128..384 with 4..12 cycles:
-// 49.0 -> 40.9 ms).
-static bool track_batch(nhp_plan* const* plans, const uint32_t* counts, uint32_t n) {
+// Where tracking pays in shared launches.  Listing the tiles is one more launch
+// of 5 us and most tiles stay active for the first cycles, so it wants launches
+// of 100 us and more: from 2^26 poses on, calls of 2 to 12 cycles take 0.46 to 1.05
+// times the time of visiting all (one to 256 plans on open maps, clutter and
+// rectangles; 60 plans of sides 128..384 with 4..12 cycles: 49.0 -> 40.9 ms).  Smaller
+// launches lose in the first cycles and gain in later ones: 2^25 poses 0.74-1.11
+// with 2 to 6 cycles, 0.61-1.06 with 8 and more; 2^24 0.77-1.16 with 2 to 6, 0.43-1.05
+// with 16 and more.  So they are tracked when the whole call makes 2^28 updates
+// per maneuver, or when tracked launches have seen the plans through their
+// first 6 cycles (cycles 7 to 12 at 2^24 poses: 0.72-0.94).
+constexpr size_t kTrackPoses = (size_t)1 << 26, kTrackUpdates = (size_t)1 << 28, kTrackLate = (size_t)1 << 24;
+constexpr uint32_t kTrackedCycles = 6;
+
+static size_t plan_poses(const nhp_plan* p) { return (size_t)p->p.nx * p->p.nx * p->p.ntheta; }
+
+// Shared launches are tracked when their plans (counts[k] > 0) hold at least
+// `least` poses together and the stamps of every one describe its volume: a plan
+// that starts without them has them cleared and all its tiles visited and stamped,
+// call after call if its volumes were handed out (six calls of a cycle each, 64
+// plans of 64^3: 3.0 ms so, 2.0 in full; four of 256^3 3.46 and 3.13).
+static bool track_batch(nhp_plan* const* plans, const uint32_t* counts, uint32_t n, size_t least) {
   size_t poses = 0;
   for (uint32_t k = 0; k < n; k++) {
     if (counts[k] == 0) continue;
-    if (!nhp::trackable(plans[k]->d)) return false;
-    poses += (size_t)plans[k]->p.nx * plans[k]->p.nx * plans[k]->p.ntheta;
+    if (!nhp::trackable(plans[k]->d) || !plans[k]->ts_valid) return false;
+    poses += plan_poses(plans[k]);
   }
-  return poses >= (size_t)1 << 24;
+  return poses >= least;
 }
 
-static int advance(nhp_batch* b, nhp_plan* const* plans, const uint32_t* steps, const uint32_t* counts, uint32_t n) {
+static int advance(nhp_batch* b, nhp_plan* const* plans, const uint32_t* steps, const uint32_t* counts, uint32_t n,
+                   size_t least) {
   int rc = NHP_OK;
   std::vector<std::vector<nhp::Pass>> passes(n);
   size_t most = 0;
@@ -507,7 +524,7 @@ static int advance(nhp_batch* b, nhp_plan* const* plans, const uint32_t* steps, 
   bool capture = false;
   for (uint32_t k = 0; k < n; k++)
     if (counts[k] > 0) capture = nhp::captured(plans[k], b->stream) || capture;
-  const bool track = !capture && track_batch(plans, counts, n);
+  const bool track = !capture && track_batch(plans, counts, n, least);
   for (uint32_t k = 0; k < n; k++) {
     if (passes[k].empty()) continue;
     if (track && (rc = nhp::track_plan(plans[k], b->stream))) return rc;
@@ -537,9 +554,12 @@ int batch_advance(nhp_batch* b, nhp_plan* const* plans, const uint32_t* steps, c
   if (rc) return rc;
   if (n == 0) return nhp::clear_error();
   if (!steps || !counts) return nhp::set_error(NHP_EINVAL, "steps or counts is NULL");
-  for (uint32_t k = 0; k < n; k++)
+  uint32_t seen = kTrackedCycles;  // cycles the stamps of all plans have seen
+  for (uint32_t k = 0; k < n; k++) {
     if (plans[k]->exposed) plans[k]->ts_valid = false;
-  return advance(b, plans, steps, counts, n);
+    if (counts[k] > 0) seen = std::min(seen, plans[k]->ts.sweeps / plans[k]->p.n_schedule);
+  }
+  return advance(b, plans, steps, counts, n, seen >= kTrackedCycles ? kTrackLate : kTrackPoses);
 }
 
 int batch_step(nhp_batch* b, nhp_plan* const* plans, const uint32_t* steps, uint32_t n) {
@@ -576,7 +596,13 @@ int batch_sweep(nhp_batch* b, nhp_plan* const* plans, const uint32_t* starts_ijt
   // cycle's last sweep shares a pass with the next cycle's first when they
   // fuse and the plan goes on.
   uint32_t most = 0;
-  for (uint32_t k = 0; k < n; k++) most = std::max(most, n_cycles[k]);
+  size_t poses = 0, updates = 0;
+  for (uint32_t k = 0; k < n; k++) {
+    most = std::max(most, n_cycles[k]);
+    poses += n_cycles[k] ? plan_poses(plans[k]) : 0;
+    updates += n_cycles[k] * plan_poses(plans[k]);
+  }
+  const size_t least = poses >= kTrackPoses || updates >= kTrackUpdates ? kTrackLate : SIZE_MAX;
   std::vector<uint32_t> done(n, 0), skip(n, 0);
   std::vector<nhp_plan*> active;
   std::vector<uint32_t> steps, counts;
@@ -600,7 +626,7 @@ int batch_sweep(nhp_batch* b, nhp_plan* const* plans, const uint32_t* starts_ijt
       done[k] += counts.back();
       skip[k] = consumed ? 1 : 0;
     }
-    rc = advance(b, active.data(), steps.data(), counts.data(), (uint32_t)active.size());
+    rc = advance(b, active.data(), steps.data(), counts.data(), (uint32_t)active.size(), least);
     if (rc) return rc;
   }
   return nhp::clear_error();

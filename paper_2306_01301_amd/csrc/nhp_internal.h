@@ -115,6 +115,7 @@ __host__ __device__ inline StampLayout stamp_layout(int nx, int nt) {
 constexpr uint32_t kTrackStale = 0xFFFFFFFFu;
 struct TrackState {
   uint32_t pass = 0;
+  uint32_t sweeps = 0;  // sweeps in those passes
   uint32_t last[6] = {0, 0, 0, 0, 0, 0};
 };
 

@@ -96,6 +96,7 @@ int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj, 
   if (ts) {
     row->tr.mode = kTrackSkip;
     ts->last[(int)pass.mu] = ++ts->pass;
+    ts->sweeps++;
   }
   return 1;
 }
@@ -234,6 +235,63 @@ void repeated_call() {
   for (nhp_plan* p : plan) plan_destroy(p);
 }
 
+// batch_advance: cycles of one call each
+std::string advance(nhp_batch* b, nhp_plan** plan, uint32_t n, int cycles) {
+  static const uint32_t steps[64] = {};
+  uint32_t counts[64];
+  for (uint32_t& c : counts) c = 6;
+  std::string out;
+  for (int c = 0; c < cycles; c++) {
+    if (batch_advance(b, plan, steps, counts, n) != NHP_OK) return plan_last_error();
+    out += route();
+  }
+  return out;
+}
+
+char sweep(nhp_batch* b, nhp_plan** plan, uint32_t n, uint32_t cycles) {
+  uint32_t start[3 * 64] = {}, n_cycles[64];
+  for (uint32_t& c : n_cycles) c = cycles;
+  for (uint32_t& s : start) s = 5;
+  route();
+  if (batch_sweep(b, plan, start, n_cycles, n) != NHP_OK) return '!';
+  return route();
+}
+
+void shared_launches() {
+  nhp_plan* plan[5];
+  uint32_t start[15] = {};
+  for (int k = 0; k < 4; k++) plan[k] = make_plan(256, 256);
+  plan[4] = make_plan(16, 16);  // too small to be tracked
+  for (uint32_t& s : start) s = 5;
+  nhp_batch* b = nullptr;
+  batch_create(5, nullptr, &b);
+  batch_init(b, plan, start, 4);
+  route();
+  printf("four, 7 cycles: %s\n", advance(b, plan, 4, 7).c_str());
+  printf("then one alone: %s\n", advance(b, plan, 1, 1).c_str());
+  batch_init(b, plan, start, 4);
+  printf("four, 5 cycles: %s\n", advance(b, plan, 4, 5).c_str());
+  printf("then one alone, then all: %s", advance(b, plan, 1, 1).c_str());
+  printf(" %s\n", advance(b, plan, 4, 1).c_str());
+  batch_init(b, plan, start, 4);
+  printf("two: %s\n", advance(b, plan, 2, 2).c_str());
+  printf("with a small one: %c\n", sweep(b, plan + 1, 4, 8));
+  printf("sweep of four, 1 cycle: %c\n", sweep(b, plan, 4, 1));
+  printf("sweep of two, 7 and 8 cycles: %c", sweep(b, plan, 2, 7));
+  printf(" %c\n", sweep(b, plan, 2, 8));
+  printf("sweep of one, 15 and 16 cycles: %c", sweep(b, plan, 1, 15));
+  printf(" %c\n", sweep(b, plan, 1, 16));
+  uint32_t* v;
+  plan_device_ptrs(plan[2], &v, nullptr);
+  batch_init(b, plan, start, 4);
+  route();
+  printf("four, one handed out: %s\n", advance(b, plan, 4, 3).c_str());
+  printf("sweep of four, one handed out: %c\n", sweep(b, plan, 4, 2));
+  printf("four more, one handed out: %s\n", advance(b, plan, 4, 2).c_str());
+  batch_destroy(b);
+  for (nhp_plan* p : plan) plan_destroy(p);
+}
+
 void extract_wait() { printf("milliseconds at 2.4 GHz: %llu\n", (unsigned long long)(nhp::kLeastWaitClocks / 2400000)); }
 
 }  // namespace
@@ -243,6 +301,7 @@ int main(int argc, char** argv) {
   if (what == "failed_list_launch") failed_list_launch();
   if (what == "extract_wait") extract_wait();
   if (what == "repeated_call") repeated_call();
+  if (what == "shared_launches") shared_launches();
   printf("wrong: %s\n", g_wrong.empty() ? "nothing" : g_wrong.c_str());
   return 0;
 }

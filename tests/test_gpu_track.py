@@ -318,3 +318,32 @@ def test_views_of_a_closed_planner():
         out.append((p.value_numpy().copy(), p.cspace_numpy().copy()))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
     assert out[0][0].min() == 0 and out[0][1].max() == 255
+
+
+def test_tracked_batches_of_mixed_plans_equal_every_pass_in_full():
+    """At least 2^26 poses in every call, of every section size and both grid kinds."""
+    scs, ps = _mixed_plans(((512, 128, FULL), (328, 256, FULL)))
+    cycles = [3 + k % 4 for k in range(len(scs))]
+    want = _in_full(scs, cycles)
+    b = P.Batch(len(scs))
+    print("sweep", flush=True)
+    for _ in range(2):
+        b.sweep(ps, [sc.start for sc in scs], cycles)
+    for p, w, sc in zip(ps, want, scs):
+        _same(p, w, (sc.nx, sc.nt))
+        p.close()
+    print("calls that go on from one another", flush=True)
+    ps = [P.planner_for(sc) for sc in scs]
+    for p, sc in zip(ps, scs):
+        p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+    b.init(ps, [sc.start for sc in scs])
+    done = [0] * len(scs)
+    for call in range(5):
+        counts = [0 if k < 7 and (k + call) % 5 == 0 else len(sc.schedule) * (1 + (k + call) % 2) for k, sc in enumerate(scs)]
+        b.advance(ps, done, counts)
+        done = [d + c for d, c in zip(done, counts)]
+    want = _in_full(scs, [d // len(sc.schedule) for d, sc in zip(done, scs)])
+    for p, w, sc in zip(ps, want, scs):
+        _same(p, w, (sc.nx, sc.nt))
+        p.close()
+    b.close()

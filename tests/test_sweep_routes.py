@@ -45,3 +45,23 @@ def test_a_repeated_shared_call_is_found_by_words(ask):
     # going through the job table byte by byte
     got = ask("repeated_call")
     assert got["route"] == "f" and got["faster than its table's bytes"] == "yes"
+
+
+def test_shared_launches_are_tracked_where_that_pays(ask):
+    """t: only the tiles that changes have reached, f: all tiles.  2^24 poses each."""
+    got = ask("shared_launches")
+    assert got == {
+        "four, 7 cycles": "ttttttt",
+        "then one alone": "t",  # after 6 cycles
+        "four, 5 cycles": "ttttt",
+        "then one alone, then all": "f f",
+        "two": "ff",
+        "with a small one": "f",
+        "sweep of four, 1 cycle": "t",
+        "sweep of two, 7 and 8 cycles": "f t",
+        "sweep of one, 15 and 16 cycles": "f t",
+        "four, one handed out": "fff",
+        "sweep of four, one handed out": "t",  # (a sweep starts from its own volume)
+        "four more, one handed out": "ff",
+        "wrong": "nothing",
+    }
