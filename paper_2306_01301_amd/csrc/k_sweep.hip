@@ -380,17 +380,7 @@ void launch_band(const SweepJob& j, hipStream_t s) {
     hipLaunchKernelGGL((xmajor_band_kernel<Q, NT, BUFS, false>), grid, block, 0, s, j);
 }
 
-// Tracking costs a row launch about 8 us (finding the active tiles, stamping
-// the last one) and a pass with every tile active about 8 % more, and saves
-// the tiles that no change has reached.  Volumes of at least 2^26 poses gain:
-// whole plans (start, now) 512^3 maze with 20 cycles 18.1 -> 13.9 ms, 1024^2
-// x 512 with 8 cycles 31.6 -> 28.3 ms, 512^2 x 256 with 6 cycles 2.88 -> 2.85
-// ms; below, launches of 10 to 35 us lose it again (384^2 x 128, 12 cycles:
-// 1.36 -> 1.52 ms; 200^2 x 72: 0.75 -> 0.89 ms).
 bool trackable(const DevPlan& d) { return xmajor_wide(d.nx); }  // (transposed tiles keep no stamps)
-bool track_sweeps(const DevPlan& d) {
-  return trackable(d) && (size_t)d.nx * d.nx * d.nt >= (size_t)1 << 26;
-}
 
 hipError_t launch_sweep(const DevPlan& d, Pass pass, hipStream_t s, TrackState* ts) {
   return launch_sweep_part(d, pass, 3, s, ts);

@@ -478,6 +478,21 @@ static hipGraphExec_t capture_passes(nhp_plan* plan, const std::vector<nhp::Pass
   return exec;
 }
 
+// Where tracking pays in the sweeps of one plan.  Every workgroup of a row launch
+// first reads the stamps of all its tiles, about 8 us, and a pass with every tile
+// active takes about 8 % more.  Times of whole sweeps of 1 to 12 cycles against
+// visiting all, on open maps, clutter, rectangles and mazes: volumes of 2^26 poses and
+// more with 136 headings and more 0.27-1.035 (above 1 at 3 and 4 cycles of open
+// maps); below, launches of 10 to 35 us lose it again (384^2 x 128, 12 cycles:
+// 1.12; 200^2 x 72: 1.19).  With at most 128 headings a tile is short and there are
+// up to 16384 of them to look through: 1024^2 x 64 0.62-1.22 with 1 to 8 cycles,
+// 768^2 x 120 0.42-1.21, 1024^2 x 128 0.46-1.09, and from 12 cycles on 0.48-1.004.
+static bool track_run(const nhp_plan* plan, uint32_t n_cycles) {
+  const nhp::DevPlan& d = plan->d;
+  if (!nhp::trackable(d) || (size_t)d.nx * d.nx * d.nt < (size_t)1 << 26) return false;
+  return d.nt > 128 || n_cycles >= 12;
+}
+
 // n_cycles cycles of the schedule as passes (consecutive turns on shared
 // curves fused, also across cycle boundaries).  A cycle's launches come from
 // a captured graph once a plan runs more than one cycle for the second time:
@@ -489,7 +504,7 @@ static int run_cycles(nhp_plan* plan, uint32_t n_cycles) {
   if (n_cycles == 0) return NHP_OK;  // (the stamps know as much, or as little, as before)
   const bool pairs = nhp::can_fuse(plan->d);
   nhp::TrackState* ts = nullptr;
-  if (!nhp::captured(plan, plan->stream) && nhp::track_sweeps(plan->d) && (plan->ts_valid || n_cycles > 1)) {
+  if (!nhp::captured(plan, plan->stream) && track_run(plan, n_cycles) && (plan->ts_valid || n_cycles > 1)) {
     int rc = nhp::track_plan(plan, plan->stream);
     if (rc) return rc;
     ts = &plan->ts;

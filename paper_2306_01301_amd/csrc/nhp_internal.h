@@ -194,9 +194,7 @@ int get_knob(int knob);
 // ts: the tracked run the pass belongs to (its pass number and the
 // maneuvers' last passes are moved on), or nullptr.
 int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj, TrackState* ts = nullptr);
-// Whether a plan's sweeps are worth tracking on their own (see k_sweep.hip),
-// and whether they can be tracked at all.
-bool track_sweeps(const DevPlan& d);
+// Whether a plan's sweeps can be tracked at all.
 bool trackable(const DevPlan& d);
 // Whether x-major jobs of grid side N take the 4-column-load kernel (batched
 // x-major launches group their jobs by it and pass it as `pow2`).

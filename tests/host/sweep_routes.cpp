@@ -75,7 +75,6 @@ namespace nhp {
 bool can_fuse(const DevPlan&) { return false; }
 bool xmajor_wide(int) { return true; }
 bool trackable(const DevPlan& d) { return d.nx >= 32; }
-bool track_sweeps(const DevPlan& d) { return trackable(d) && (size_t)d.nx * d.nx * d.nt >= (size_t)1 << 26; }
 int set_knob(int, int) { return NHP_OK; }
 int get_knob(int) { return 0; }
 int set_section_steps(int, int) { return NHP_OK; }
@@ -204,6 +203,25 @@ void failed_list_launch() {
   for (nhp_plan* p : plan) plan_destroy(p);
 }
 
+char swept(nhp_plan* p, uint32_t cycles) {
+  route();
+  sweep_n_turns(p, 5, 5, 0, cycles);
+  return route();
+}
+
+void whole_sweeps() {
+  const struct {
+    uint32_t n, nt, cycles[3];
+  } asked[] = {{1024, 64, {1, 11, 12}}, {1024, 128, {4, 11, 12}}, {720, 136, {1, 3, 20}}, {512, 256, {1, 3, 20}}, {512, 248, {1, 20, 60}}};
+  for (const auto& a : asked) {
+    nhp_plan* p = make_plan(a.n, a.nt);
+    printf("%ux%u:", a.n, a.nt);
+    for (uint32_t c : a.cycles) printf(" %c", swept(p, c));
+    printf("\n");
+    plan_destroy(p);
+  }
+}
+
 double now() { return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count(); }
 
 // A call that repeats an earlier one against hashing the bytes of its job table
@@ -301,6 +319,7 @@ int main(int argc, char** argv) {
   if (what == "failed_list_launch") failed_list_launch();
   if (what == "extract_wait") extract_wait();
   if (what == "repeated_call") repeated_call();
+  if (what == "whole_sweeps") whole_sweeps();
   if (what == "shared_launches") shared_launches();
   printf("wrong: %s\n", g_wrong.empty() ? "nothing" : g_wrong.c_str());
   return 0;

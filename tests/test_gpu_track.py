@@ -347,3 +347,25 @@ def test_tracked_batches_of_mixed_plans_equal_every_pass_in_full():
         _same(p, w, (sc.nx, sc.nt))
         p.close()
     b.close()
+
+
+@pytest.mark.parametrize("n,nt", [(1000, 72), (1024, 64), (760, 120), (736, 128)])
+def test_tracked_sweeps_of_few_headings_equal_every_pass_in_full(n, nt):
+    """Short sections: tracked from 12 cycles on."""
+    sc = _scene(n, nt, n + nt, FULL)
+    p = P.planner_for(sc)
+    p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+    p.sweep(sc.start, 0)
+    _passes(p, FULL, 12)
+    want = p.value.clone()
+    print("tracked %s" % ((n, nt),), flush=True)
+    p.sweep(sc.start, 12)
+    _same(p, want, "sweep")
+    i, j, T = sc.start
+    starts = [(i, j, T, 700, -1), (i + 2, j, T, 100, RB), (i, j + 3, (T + 7) % nt, 0, SF), (i, j, 0, 50, LB)]
+    p.sweep_from_set(starts, 0)
+    _passes(p, FULL, 12)
+    want.copy_(p.value)
+    p.sweep_from_set(starts, 12)
+    _same(p, want, "start set")
+    p.close()

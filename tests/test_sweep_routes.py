@@ -65,3 +65,10 @@ def test_shared_launches_are_tracked_where_that_pays(ask):
         "four more, one handed out": "ff",
         "wrong": "nothing",
     }
+
+
+def test_whole_sweeps_are_tracked_where_that_pays(ask):
+    """As above, at three numbers of cycles each."""
+    got = ask("whole_sweeps")
+    assert got == {"1024x64": "f f t", "1024x128": "f f t", "720x136": "t t t", "512x256": "t t t", "512x248": "f f f",
+                   "wrong": "nothing"}
