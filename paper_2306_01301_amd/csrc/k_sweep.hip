@@ -67,13 +67,9 @@ int knob(int k, int builtin) {
   return v ? v : builtin;
 }
 
-// Resident workgroups for a row launch: 256 CUs times the workgroups of
-// `waves` waves that fit one CU (built-in: at most 16 waves per CU at these
-// register counts, 32 for the small sections).
+// Resident workgroups for a row launch, on 256 CUs.
 int row_grid(int blocks, int waves, int P) {
-  const int builtin = (P >= 32 ? 16 : 32) / waves;
-  const int per_cu = knob(NHP_KNOB_ROW_WG_PER_CU, builtin > 0 ? builtin : 1);
-  const int cap = 256 * per_cu;
+  const int cap = 256 * knob(NHP_KNOB_ROW_WG_PER_CU, row_workgroups(waves, P));
   return blocks < cap ? blocks : cap;
 }
 

@@ -188,6 +188,15 @@ int set_section_steps(int len, int P);
 constexpr int kKnobs = 4;
 int set_knob(int knob, int value);
 int knob(int knob, int builtin);                  // the knob's value, or the built-in one
+// Workgroups of `waves` waves that a row launch keeps on a CU: as many as its wave
+// slots take at these registers (16, and 32 for the small sections), except that of
+// three workgroups of 10 waves, 30 of the 32 slots, only two fit beside each other
+// (they are dealt to four SIMDs of 8 slots): the tiles of the third then start when the
+// others have ended.  Fused pass of 80 headings, 920^2 maze: 145 us asking for 3,
+// 121 for 2; 512^2 43 and 36; single turn 97 and 82.
+constexpr int row_workgroups(int waves, int P) {
+  return P < 32 && waves == 10 ? 2 : (P >= 32 ? 16 : 32) / waves > 0 ? (P >= 32 ? 16 : 32) / waves : 1;
+}
 int row_grid(int blocks, int waves, int P);       // workgroups of a row launch
 int xmajor_grid(int blocks, int per_cu);          // and of an x-major launch
 int get_knob(int knob);

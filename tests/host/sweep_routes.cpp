@@ -310,6 +310,14 @@ void shared_launches() {
   for (nhp_plan* p : plan) plan_destroy(p);
 }
 
+void workgroups() {
+  for (int P : {8, 32}) {
+    printf("%d steps:", P);
+    for (int w = 1; w <= 16; w++) printf(" %d", nhp::row_workgroups(w, P));
+    printf("\n");
+  }
+}
+
 void extract_wait() { printf("milliseconds at 2.4 GHz: %llu\n", (unsigned long long)(nhp::kLeastWaitClocks / 2400000)); }
 
 }  // namespace
@@ -320,6 +328,7 @@ int main(int argc, char** argv) {
   if (what == "extract_wait") extract_wait();
   if (what == "repeated_call") repeated_call();
   if (what == "whole_sweeps") whole_sweeps();
+  if (what == "row_workgroups") workgroups();
   if (what == "shared_launches") shared_launches();
   printf("wrong: %s\n", g_wrong.empty() ? "nothing" : g_wrong.c_str());
   return 0;

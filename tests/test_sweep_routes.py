@@ -72,3 +72,10 @@ def test_whole_sweeps_are_tracked_where_that_pays(ask):
     got = ask("whole_sweeps")
     assert got == {"1024x64": "f f t", "1024x128": "f f t", "720x136": "t t t", "512x256": "t t t", "512x248": "f f f",
                    "wrong": "nothing"}
+
+
+def test_row_workgroups_fit_side_by_side(ask):
+    # by waves per workgroup, 1 to 16; two, not three, of 10 waves
+    got = ask("row_workgroups")
+    assert got["8 steps"] == "32 16 10 8 6 5 4 4 3 2 2 2 2 2 2 2"
+    assert got["32 steps"] == "16 8 5 4 3 2 2 2 1 1 1 1 1 1 1 1"
