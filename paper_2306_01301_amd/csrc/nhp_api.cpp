@@ -487,10 +487,19 @@ static hipGraphExec_t capture_passes(nhp_plan* plan, const std::vector<nhp::Pass
 // 1.12; 200^2 x 72: 1.19).  With at most 128 headings a tile is short and there are
 // up to 16384 of them to look through: 1024^2 x 64 0.62-1.22 with 1 to 8 cycles,
 // 768^2 x 120 0.42-1.21, 1024^2 x 128 0.46-1.09, and from 12 cycles on 0.48-1.004.
+// Cycles that go on from a volume have the stamps of the ones before them, or
+// none.  Soon after the start nearly every tile is active, and without stamps the
+// first cycle visits all: up to 8 cycles in all, resumes took up to 1.18 times
+// visiting all (656^2 x 160, one cycle after four), 1024^2 x 64 up to 1.33.  From 8 on (12
+// with few headings) 0.04-1.05.  Sections of 64 steps (more than 512 headings) lose up to
+// 1.08 in mazes however late.
 static bool track_run(const nhp_plan* plan, uint32_t n_cycles) {
   const nhp::DevPlan& d = plan->d;
   if (!nhp::trackable(d) || (size_t)d.nx * d.nx * d.nt < (size_t)1 << 26) return false;
-  return d.nt > 128 || n_cycles >= 12;
+  const bool from_start = plan->ts_valid && plan->ts.sweeps == 0;
+  const uint64_t cycles = (uint64_t)n_cycles + (plan->ts_valid ? plan->ts.sweeps / plan->p.n_schedule : 0);
+  if (d.nt <= 128) return cycles >= 12;
+  return from_start || (cycles >= 8 && d.nt <= 512);
 }
 
 // n_cycles cycles of the schedule as passes (consecutive turns on shared
@@ -504,7 +513,7 @@ static int run_cycles(nhp_plan* plan, uint32_t n_cycles) {
   if (n_cycles == 0) return NHP_OK;  // (the stamps know as much, or as little, as before)
   const bool pairs = nhp::can_fuse(plan->d);
   nhp::TrackState* ts = nullptr;
-  if (!nhp::captured(plan, plan->stream) && track_run(plan, n_cycles) && (plan->ts_valid || n_cycles > 1)) {
+  if (!nhp::captured(plan, plan->stream) && track_run(plan, n_cycles)) {
     int rc = nhp::track_plan(plan, plan->stream);
     if (rc) return rc;
     ts = &plan->ts;

@@ -102,7 +102,7 @@ int make_sweep_jobs(const DevPlan& d, Pass pass, SweepJob* row, SweepJob* xmaj, 
 
 hipError_t launch_sweep(const DevPlan& d, Pass pass, hipStream_t, TrackState* ts) {
   SweepJob row, xm;
-  make_sweep_jobs(d, pass, &row, &xm, ts);
+  (void)make_sweep_jobs(d, pass, &row, &xm, ts);
   (ts ? g_tracked : g_full)++;
   return hipSuccess;
 }
@@ -222,6 +222,47 @@ void whole_sweeps() {
   }
 }
 
+char resumed(nhp_plan* p, uint32_t cycles) {
+  route();
+  sweep_resume(p, cycles);
+  return route();
+}
+
+void resumes() {
+  nhp_plan* p = make_plan(512, 256);
+  printf("after 2, 5 more: %c", swept(p, 2));
+  printf(" %c\n", resumed(p, 5));
+  printf("after 2, 6 more, 1 more: %c", swept(p, 2));
+  printf(" %c", resumed(p, 6));
+  printf(" %c\n", resumed(p, 1));
+  sweep_one(p, 1);
+  printf("after one maneuver, 7 more, 8 more: %c", resumed(p, 7));
+  printf(" %c\n", resumed(p, 8));
+  printf("after 0, 0, 3 more: %c", swept(p, 0));
+  printf(" %c", resumed(p, 0));
+  printf(" %c\n", resumed(p, 3));
+  sweep_one(p, 1);
+  resumed(p, 0);
+  printf("after one maneuver and 0, 1 more: %c\n", resumed(p, 1));
+  uint32_t* v;
+  plan_device_ptrs(p, &v, nullptr);
+  printf("handed out, 9, 1 more, 8 more: %c", swept(p, 9));
+  printf(" %c", resumed(p, 1));
+  printf(" %c\n", resumed(p, 8));
+  plan_destroy(p);
+  p = make_plan(1024, 64);
+  printf("few headings, after 12, 1 more: %c", swept(p, 12));
+  printf(" %c\n", resumed(p, 1));
+  printf("after 11, 11 more, 12 more: %c", swept(p, 11));
+  printf(" %c", resumed(p, 11));
+  printf(" %c\n", resumed(p, 12));
+  plan_destroy(p);
+  p = make_plan(264, 1000);
+  printf("64-step sections, after 12, 12 more: %c", swept(p, 12));
+  printf(" %c\n", resumed(p, 12));
+  plan_destroy(p);
+}
+
 double now() { return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count(); }
 
 // A call that repeats an earlier one against hashing the bytes of its job table
@@ -329,6 +370,7 @@ int main(int argc, char** argv) {
   if (what == "repeated_call") repeated_call();
   if (what == "whole_sweeps") whole_sweeps();
   if (what == "row_workgroups") workgroups();
+  if (what == "resumes") resumes();
   if (what == "shared_launches") shared_launches();
   printf("wrong: %s\n", g_wrong.empty() ? "nothing" : g_wrong.c_str());
   return 0;

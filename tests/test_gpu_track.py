@@ -369,3 +369,31 @@ def test_tracked_sweeps_of_few_headings_equal_every_pass_in_full(n, nt):
     p.sweep_from_set(starts, 12)
     _same(p, want, "start set")
     p.close()
+
+
+def test_tracked_resumes_equal_every_pass_in_full():
+    """Late enough to be tracked, with stamps from before and without."""
+    sc = _scene(512, 256, 15, FULL).with_(image=scenes.maze(np.random.default_rng(15), 16, 32, 4), start=(18, 18, 0))
+    want = {n: _in_full([sc], [n])[0] for n in (11, 20)}
+    p = P.planner_for(sc)
+    p.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+    p.sweep(sc.start, 7)
+    p.resume(1)
+    p.resume(3)
+    p.resume(0)
+    for mu in FULL:
+        p.sweep_one(mu)
+    p.resume(8)
+    _same(p, want[20], "sweep, resumes, single passes, resume")
+    p.sweep(sc.start, 3)  # (its volumes have now been handed out)
+    p.resume(8)
+    _same(p, want[11], "resume of eight cycles")
+    p.close()
+    # a whole sweep, then resumes that go on from its stamps
+    q = P.planner_for(sc)
+    q.render(torch.from_numpy(sc.image).cuda(), sc.vehicle)
+    q.sweep(sc.start, 7)
+    q.resume(1)
+    q.resume(3)
+    _same(q, want[11], "sweep and resumes")
+    q.close()

@@ -79,3 +79,19 @@ def test_row_workgroups_fit_side_by_side(ask):
     got = ask("row_workgroups")
     assert got["8 steps"] == "32 16 10 8 6 5 4 4 3 2 2 2 2 2 2 2"
     assert got["32 steps"] == "16 8 5 4 3 2 2 2 1 1 1 1 1 1 1 1"
+
+
+def test_resumes_are_tracked_where_that_pays(ask):
+    got = ask("resumes")
+    assert got == {
+        "after 2, 5 more": "t f",
+        "after 2, 6 more, 1 more": "t t t",
+        "after one maneuver, 7 more, 8 more": "f t",
+        "after 0, 0, 3 more": "- - t",  # (still from the start)
+        "after one maneuver and 0, 1 more": "f",
+        "handed out, 9, 1 more, 8 more": "t f t",
+        "few headings, after 12, 1 more": "t t",
+        "after 11, 11 more, 12 more": "f f t",
+        "64-step sections, after 12, 12 more": "t f",
+        "wrong": "nothing",
+    }
