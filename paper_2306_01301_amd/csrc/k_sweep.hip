@@ -18,7 +18,7 @@ __global__ __launch_bounds__(1024) void row_sweep_kernel(SweepJob job) {
   __shared__ RowShared sh;
   StepStore<P, false> none;
   StepKeep<P, false> keep(none);
-  keep.set_geo(turn_geo<P>(job));
+  keep.set_geo(turn_geo<P, false>(job));
   for (int b = blockIdx.x; b < job.blocks; b += gridDim.x) {
     __syncthreads();
     row_sweep_tile<P, FUSED, GUARD, POW2, false>(job, tile_of(b, job.blocks, job.order), 0, sh, keep, -1);
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(1024) void row_track_kernel(SweepJob job) {
   __shared__ ActiveTiles at;
   __shared__ StepStore<P, LDS> store;
   StepKeep<P, LDS> keep(store);
-  const TurnGeo geo = turn_geo<P>(job);  // (on its way while the active tiles are found)
+  const TurnGeo geo = turn_geo<P, true>(job);  // (on its way while the active tiles are found)
   if (threadIdx.x == 0) sh.tr = job.tr;  // (read after the tiles' barriers)
   const bool skip = job.tr.mode == kTrackSkip;
   // with a workgroup per tile each looks at its own tile's stamp only

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(1024) void row_track_batch_kernel(const SweepJob* _
         swept = -1;
         __syncthreads();
       }
-      keep.set_geo(turn_geo<P>(jobs[j]));
+      keep.set_geo(turn_geo<P, true>(jobs[j]));
       if (threadIdx.x == 0) sh.tr = jobs[j].tr;  // (read after the tile's barriers)
       jg = j;
     }
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(1024) void row_sweep_batch_kernel(const SweepJob* _
     const int j = __builtin_amdgcn_readfirstlane(find_job(jobs, n_jobs, t));
     const SweepJob job = jobs[j];
     if (j != jg) {
-      keep.set_geo(turn_geo<P>(job));
+      keep.set_geo(turn_geo<P, false>(job));
       jg = j;
     }
     row_sweep_tile<P, FUSED, GUARD, POW2, false>(job, t - job.first_block, 0, sh, keep, -1);

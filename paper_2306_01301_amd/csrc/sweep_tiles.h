@@ -84,13 +84,19 @@ __device__ __forceinline__ uint32_t row_cell(uint32_t g, uint32_t x, uint32_t sh
 
 // bits |= any ? bit : 0 on scalar registers (any and bits are the same in all
 // lanes; written out because the compiler folds such bits through vector
-// registers, or keeps every mask live to the end).
+// registers, or keeps every mask live to the end).  A lone maneuver without
+// stamps has the registers for it, and there the compiler's own order is the
+// faster one (single turn 512^2 x 256: 67.0 us, written out 68.5): note_lone.
 __device__ __forceinline__ void set_if(uint32_t& bits, uint32_t any, uint32_t bit) {
   uint32_t t;
   asm("s_cmp_lg_u32 %2, 0\n\ts_cselect_b32 %1, %3, 0\n\ts_or_b32 %0, %0, %1"
       : "+s"(bits), "=&s"(t)
       : "s"(any), "i"(bit)
       : "scc");
+}
+
+__device__ __forceinline__ void note_lone(uint32_t& bits, uint64_t mask, int k) {
+  bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)(bits | ((mask != 0ull ? 1u : 0u) << k)));
 }
 
 constexpr int kBufferWord3 = 0x00020000;  // descriptor word 3 for untyped access on gfx9-family GPUs
@@ -330,8 +336,10 @@ __device__ __forceinline__ void scan_section(const SweepJob& a, const RowBuffers
     if (TRACK) {
       set_if(lo, (uint32_t)m, 1u << k);
       set_if(hi, (uint32_t)(m >> 32), 1u << k);
-    } else {
+    } else if (FUSED) {
       set_if(lo, (uint32_t)m | (uint32_t)(m >> 32), 1u << k);
+    } else {
+      note_lone(lo, m, k);
     }
   };
   static_assert(P <= 32, "one bit per step");
@@ -445,7 +453,10 @@ __device__ __forceinline__ void scan_section_wide(const SweepJob& a, const RowBu
   uint32_t changed[2] = {};
   auto note = [&](int k, uint32_t before, uint32_t after) {
     const uint64_t m = __builtin_amdgcn_ballot_w64(after != before);
-    set_if(changed[k >> 5], (uint32_t)m | (uint32_t)(m >> 32), 1u << (k & 31));
+    if (FUSED)
+      set_if(changed[k >> 5], (uint32_t)m | (uint32_t)(m >> 32), 1u << (k & 31));
+    else
+      note_lone(changed[k >> 5], m, k & 31);
   };
   uint32_t (*hi)[64] = upper[wave];
   uint32_t u[H], packed[P / 4];
@@ -590,27 +601,32 @@ __device__ __forceinline__ void scan_section_wide(const SweepJob& a, const RowBu
 // are issued while the previous tile's stores are still draining (a global
 // read there would first wait for every earlier store).
 struct TurnGeo {
-  // shift (column offset of the curve through x' = 0), row offset of that
-  // curve from y', and column offset of the other circles: 10 bits each; top
-  // bit: the plane's straights are x-major
+  // shift (column offset of the curve through x' = 0); tracked sweeps, 10 bits
+  // each: shift, row offset of that curve from y', column offset of the other
+  // circles, and the top bit: the plane's straights are x-major
   uint32_t own;
-  // tracked sweeps: row offset of the other circles and slot of the plane (10
-  // bits each), slope of the plane (straight_slope, 12 bits)
+  // row offset of the curve from y'; tracked sweeps: row offset of the other
+  // circles and slot of the plane (10 bits each), slope of the plane
+  // (straight_slope, 12 bits)
   uint32_t other;
 };
-template <int P>
+// Without stamps the two words are the tables' own, so nothing waits for them
+// before the first tile's set-up (packed there too, single turns took 0.3-0.5 us
+// more per launch: 256^2 x 128 9.0 -> 9.4 us, 384^2 x 128 18.5 -> 20.3).
+template <int P, bool TRACK>
 __device__ __forceinline__ TurnGeo turn_geo(const SweepJob& a) {
   TurnGeo g{0u, 0u};
   const int L = a.L, N = a.N, s = threadIdx.x;
   if (a.cyclic && s < ((L + P - 1) / P) * P) {
     const int sc = s < L ? s : L - 1;  // steps past the curve repeat the last one
     const int T = a.dir ? sc : (L - 1 - sc);
-    g.own = (uint32_t)as_global(a.offx)[T] | ((uint32_t)as_global(a.offy)[T] << 10);
-    if (a.tr.mode != kTrackOff) {
+    g.own = (uint32_t)as_global(a.offx)[T];
+    g.other = (uint32_t)as_global(a.offy)[T];
+    if constexpr (TRACK) {
       const GlobalPtr<const int32_t> o = as_global(a.tr.other_off);
       const int k = straight_slope(as_global(a.skew)[(size_t)T * N + N - 1], N);
       const uint32_t slot = (uint32_t)as_global(a.tr.slot)[T];
-      g.own |= ((uint32_t)o[T] << 20) | (slot < (uint32_t)a.tr.n_planes_x ? 1u << 31 : 0u);
+      g.own |= (g.other << 10) | ((uint32_t)o[T] << 20) | (slot < (uint32_t)a.tr.n_planes_x ? 1u << 31 : 0u);
       g.other = (uint32_t)o[L + T] | (slot << 10) | ((uint32_t)k << 20);
     }
   }
@@ -758,8 +774,8 @@ __device__ __forceinline__ void row_sweep_tile(const SweepJob& a, int tile, int 
       const TurnGeo g = keep.geo();
       const int sc = s < L ? s : L - 1;
       Tn = (uint32_t)(dir ? sc : (L - 1 - sc)) * (uint32_t)N;
-      shift = (int)(g.own & 1023u);
-      row = outer + (int)((g.own >> 10) & 1023u);
+      shift = (int)(TRACK ? g.own & 1023u : g.own);
+      row = outer + (int)(TRACK ? (g.own >> 10) & 1023u : g.other);
       row -= (row >= N) ? N : 0;
     } else {
       Tn = (uint32_t)T0 * (uint32_t)N;
