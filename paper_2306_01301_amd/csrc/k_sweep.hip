@@ -357,14 +357,17 @@ hipError_t launch_force_walls(const DevPlan& d, hipStream_t s) {
 }
 
 // Columns per chunk of a band launch.  A chunk costs the latency of its loads
-// (one chunk ahead) and three barriers whatever its width, so a launch of few
-// tiles, at most about one per CU at a time, takes half as many chunks of 64
-// columns with 8 waves: 34 tiles (64^2 x 64) 8.1 -> 6.4 us, 152 (200^2 x 72)
-// 18.3 -> 15.0, 396 (384^2 x 128) 33.8 -> 28.2.  With more tiles than that the
-// narrow chunks of several tiles per CU hide each other's latency: 520 tiles
-// (256^2 x 256) 26.9 us against 29.9, 2064 (512^3) 105 against 131.  (Chunks of
-// 128 columns with 16 waves: 8.8, 16.0, 41.5 and 42.3 us on the first four.)
-constexpr int kFewBandTiles = 448;
+// (one chunk ahead) and three barriers whatever its width, so a launch of at most
+// two tiles per CU takes half as many chunks of 64 columns with 8 waves: 34 tiles
+// (64^2 x 64) 8.1 -> 6.4 us, 152 (200^2 x 72) 18.3 -> 15.0, 396 (384^2 x 128) 33.8 -> 28.2.
+// With more tiles than that the narrow chunks of several tiles per CU hide each
+// other's latency.  Time of 64 columns over 32, passes that change nothing and passes
+// that do, at 14 sides from 128 to 1024: 388 to 510 tiles 0.76-1.00 and 0.79-0.92
+// (1000^2 x 56, 480 tiles: 89.9 -> 68.7 and 98 -> 79 us), 516 to 800 tiles 1.02-1.23
+// and 1.02-1.14, but 0.93-1.03 and 1.04-1.05 at 1000^2.  (Chunks of 128 columns with 16 waves:
+// 8.8, 16.0, 41.5 us and, at 520 tiles, 42.3 against 26.9.)  Shared launches, made for
+// many plans, keep the narrow chunks.
+constexpr int kFewBandTiles = 2 * 256;
 bool wide_chunks(const SweepJob& j) { return j.N >= 64 && j.blocks <= kFewBandTiles; }
 
 template <int Q, int NT, int BUFS>

@@ -171,3 +171,10 @@ def test_extract_workgroups_agree(n, nt, schedule):
         assert r % 2 or not isinstance(want, int)
     batch.close()
     pl.close()
+
+
+# the last sides of two x-major tiles per compute unit (64-column chunks) and the
+# first of more: 456, 510, 516 and 540 tiles
+@pytest.mark.parametrize("n,nt", [(256, 224), (320, 200), (128, 512), (328, 176)])
+def test_straights_around_two_tiles_per_unit_match_oracle(n, nt):
+    test_straight_chunks_match_oracle(n, nt)
