@@ -91,8 +91,11 @@ size_t plan_workspace_bytes(const nhp_params* params);
 
 /* Builds the tables of eqs. (11)-(31) on the host and uploads them.
  * d_workspace: caller-owned device memory of at least plan_workspace_bytes()
- *   bytes, 256-byte aligned, alive until plan_destroy; NULL lets the library
- *   allocate (and free) it.
+ *   bytes, 256-byte aligned, alive until plan_destroy and the plan's own: the
+ *   caller may write the two volumes (plan_device_ptrs) and nothing else in it,
+ *   and a copy of the whole put back later is not a checkpoint (the library
+ *   knows on the host what the rest holds).  NULL lets the library allocate
+ *   (and free) it.
  * stream: hipStream_t the plan enqueues on (NULL = default stream).
  * Errors: NHP_EINVAL (params), NHP_ENOMEM (workspace too small), NHP_EHIP. */
 int plan_create(const nhp_params* params, void* d_workspace, size_t workspace_bytes, void* stream,

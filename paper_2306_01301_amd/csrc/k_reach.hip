@@ -512,7 +512,7 @@ hipError_t launch_reach_start(const ReachDev& r, uint32_t start_index, hipStream
   return hipGetLastError();
 }
 
-// The straight kernel's LDS can exceed the default dynamic limit (109 KB at
+// The straight kernel's LDS can exceed the default dynamic limit (111 KB at
 // N = 512); set once per device before any launch or capture.
 hipError_t prepare_reach_kernels() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(reach_straight_kernel),

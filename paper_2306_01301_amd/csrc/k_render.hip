@@ -96,7 +96,7 @@ __device__ __forceinline__ void max_over(const uint8_t* __restrict__ src, const 
 }
 
 // One render job per plan; a block covers kRenderRows rows of one plane:
-// block -> (plane, row group); its threads walk the rows' 4-pose groups.
+// block -> (plane, row group); its threads walk the rows' groups of 4 W poses.
 constexpr int kRenderRows = 16;
 
 __device__ __forceinline__ int find_render_job(const RenderJob* __restrict__ jobs, int n_jobs, int t) {
@@ -340,7 +340,7 @@ int render_blocks(int N, int nt) { return ((N + kRenderRows - 1) / kRenderRows) 
 hipError_t launch_render(const DevPlan& d, const uint8_t* image, int n_side, int n_len, hipStream_t s) {
   RenderJob r{};
   r.image = image;
-  r.side = reinterpret_cast<uint8_t*>(d.V);  // N_R bytes of the 4 N_R-byte value volume
+  r.side = reinterpret_cast<uint8_t*>(d.V);  // 2 N_R bytes (padded rows), then the padded image: 2 N^2, of the 4 N_R-byte value volume
   r.B = d.B;
   r.taps = d.taps;
   r.N = d.nx;
